@@ -344,10 +344,19 @@ hipError_t launch_tsweep(const SweepL& a, int ntiles, hipStream_t s) {
 // region with a halo of H = 2 A, A = APPS + RES (64 - 2H output columns,
 // NW NK - 2H output rows); each wave keeps its NK rows in registers across the
 // applications, whose valid region shrinks by 2 per application (D and
-// collision need one neighbour, the pull one more).  Between applications only
-// the first ghost row/column of D must be restored by reflection (the loaded
-// ghosts were reflected copies; after an application they hold unused
-// values): columns by a lane permutation, rows through LDS.
+// collision need one neighbour, the pull one more).
+// Walls: these launches are bound by one block's chain of dependent phases on
+// depths of few cells, and nearly every block there holds a wall.  So the
+// rules cost no branch, barrier or global load inside an application: the
+// divergence's ghost is the wall cell itself (an index), a wall population is
+// read from its mirror image or its opposite by a selected LDS offset, the
+// reference's share joins the correction that every pull adds anyway, and the
+// halfway rules' data wait in LDS.  Against per-lane branches over wall types,
+// a ghost-row pass behind its own barrier and loads of the data in every
+// application, a 64^2 level's launch of four applications drops from 14.9 to
+// 12.3 us (with the restriction from 15.4 to 13.1), the 512^2 pair from 16.2
+// to 15.0 us and the 512^2 FP32-shifted step from 580 to 515 us; periodic
+// levels, which have no walls, take 11.0 and 13.3 us.
 // R64: shifted storage whose references may be FP64 (FP64 populations, or a
 // problem above the size where FP32 references lose accuracy); without it the
 // reference arithmetic is FP32 only.
@@ -371,6 +380,13 @@ __global__ __launch_bounds__((kWave * sweepn_waves<T, SHIFT, APPS + RES, ALT>())
   __shared__ std::conditional_t<SHIFT, double, T> sEd[SHIFT ? 2 : 1][SHIFT ? RR : 1][RX];
   float (*sEf)[SHIFT ? RR : 1][RX] = reinterpret_cast<float (*)[SHIFT ? RR : 1][RX]>(sEd);
   __shared__ double sRed[2 * NW];
+  // data of the halfway rules (finest level): the three populations entering
+  // through the bottom and the top at each region column, and through the left
+  // and the right at each region row
+  using BcT = std::conditional_t<R64, double, T>;
+  __shared__ BcT sBy[2][3][FINE ? RX : 1];
+  __shared__ BcT sBx[2][3][FINE ? RR : 1];
+  constexpr int PS = (RR - 2) * RX;  // plane stride of sS
 
   const int2 te = a.tiles[blockIdx.x];
   const ProbD& P = a.probs[te.x];
@@ -450,20 +466,44 @@ __global__ __launch_bounds__((kWave * sweepn_waves<T, SHIFT, APPS + RES, ALT>())
     }
   }
 
-  // lane holding the reflection of this lane's first ghost column
-  int xm = lane;
-  if (!perx && x == -1) xm = lane + 1;
-  if (!perx && x == nx) xm = lane - 1;
-  const bool ywall_lo = !pery && y0 - H < 0, ywall_hi = !pery && y0 + TY + H > ny;
   // does the pull region (columns and rows [2, RX - 2) x [2, RR - 2)) hold a
   // wall cell?  Tiles that hold none skip every boundary rule.
   const int xa = tx * TXO - H + 2, xb = xa + RX - 5, ya = y0 - H + 2, yb = ya + RR - 5;
-  const bool bnd = (!perx && ((xa <= 0 && xb >= 0) || (xa <= nx - 1 && xb >= nx - 1))) ||
-                   (!pery && ((ya <= 0 && yb >= 0) || (ya <= ny - 1 && yb >= ny - 1)));
+  const bool atL = !perx && xa <= 0 && xb >= 0, atR = !perx && xa <= nx - 1 && xb >= nx - 1;
+  const bool atB = !pery && ya <= 0 && yb >= 0, atT = !pery && ya <= ny - 1 && yb >= ny - 1;
+  const bool bnd = atL || atR || atB || atT;
+  // wall rules by side (uniform): symmetry walls mirror, the others take a
+  // halfway rule at the cell itself (Dirichlet bounces back, traction
+  // anti-bounces back) with the wall's data
+  const int elL = P.el[kLeft], elR = P.el[kRight], elB = P.el[kBottom], elT = P.el[kTop];
+  const bool symL = elL == kElSymmetry, symR = elR == kElSymmetry, symB = elB == kElSymmetry, symT = elT == kElSymmetry;
+  const bool half = (atL && !symL) || (atR && !symR) || (atB && !symB) || (atT && !symT);
+  if (FINE && half) {
+    for (int i = threadIdx.x; i < 6 * RX + 6 * RR; i += kWave * NW) {
+      const bool isy = i < 6 * RX;
+      const int e = isy ? i : i - 6 * RX, n = isy ? RX : RR;
+      const int sd = e / (3 * n), m = e / n % 3, at = e % n;  // side, population of the side, column or row
+      // populations entering: bottom 1 4 5, top 3 6 7, left 0 4 7, right 2 5 6
+      const int q = isy ? (sd ? (m == 0 ? 3 : m + 5) : (m == 0 ? 1 : m + 3))
+                        : (sd ? (m == 0 ? 2 : m + 4) : (m == 0 ? 0 : 3 * m + 1));
+      const double* bc = P.elbc[isy ? (sd ? kTop : kBottom) : (sd ? kRight : kLeft)];
+      const int z = (isy ? tx * TXO : y0) - H + at, nz = isy ? nx : ny;
+      const bool pz = isy ? perx : pery;
+      const bool on = bc && (pz ? z >= -H && z < nz + H : z >= 0 && z < nz);
+      const BcT v = on ? BcT(bc[8 * (int64_t)ghost_map(z, nz, pz) + q]) : BcT(0);
+      if (isy)
+        sBy[sd][m][FINE ? at : 0] = v;
+      else
+        sBx[sd][m][FINE ? at : 0] = v;
+    }
+  }
 
   const T gam = k.gamma, omg = T(1) - k.gamma;
   const double inv_gam = 1.0 / P.gamma;
-  const int lm = clampi(col - 1, 0, RX - 1), lp = clampi(col + 1, 0, RX - 1);
+  // columns of the divergence's neighbours; at a wall the ghost holds the even
+  // reflection, which is the wall cell itself
+  const int lm = (!perx && x == 0) ? col : clampi(col - 1, 0, RX - 1);
+  const int lp = (!perx && x == nx - 1) ? col : clampi(col + 1, 0, RX - 1);
   double acc_r = 0.0, acc_g = 0.0;
   // shifted storage: the pull's correction per direction, the source's
   // reference minus this cell's in the rest equilibrium of the population
@@ -482,19 +522,7 @@ __global__ __launch_bounds__((kWave * sweepn_waves<T, SHIFT, APPS + RES, ALT>())
 #pragma unroll
     for (int kk = 0; kk < NK; ++kk) {
       const int j = (w + NW * kk) * S + sub;
-      T dv = k.kD * el_ms(G[kk]);
-      if (app > 0) dv = __shfl(dv, xm, kWave);
-      if (j >= e && j < RR - e) sD[j][col] = dv;
-    }
-    if (app > 0 && (ywall_lo || ywall_hi)) {
-      __syncthreads();
-#pragma unroll
-      for (int kk = 0; kk < NK; ++kk) {
-        const int j = (w + NW * kk) * S + sub;
-        const int y = y0 - H + j;
-        if (ywall_lo && y == -1) sD[j][col] = sD[j + 1][col];
-        if (ywall_hi && y == ny) sD[j][col] = sD[j - 1][col];
-      }
+      if (j >= e && j < RR - e) sD[j][col] = k.kD * el_ms(G[kk]);
     }
     __syncthreads();
     // ---- self-force and collision
@@ -502,9 +530,16 @@ __global__ __launch_bounds__((kWave * sweepn_waves<T, SHIFT, APPS + RES, ALT>())
     for (int kk = 0; kk < NK; ++kk) {
       const int j = (w + NW * kk) * S + sub;
       if (j >= e + 1 && j < RR - e - 1) {
-        T v[3][3] = {{sD[j - 1][lm], sD[j - 1][col], sD[j - 1][lp]},
-                     {sD[j][lm], sD[j][col], sD[j][lp]},
-                     {sD[j + 1][lm], sD[j + 1][col], sD[j + 1][lp]}};
+        T v[3][3] = {{T(0), T(0), T(0)}, {sD[j][lm], T(0), sD[j][lp]}, {T(0), T(0), T(0)}};  // the centre is not used
+        if (!(atB || atT)) {
+          v[0][0] = sD[j - 1][lm], v[0][1] = sD[j - 1][col], v[0][2] = sD[j - 1][lp];
+          v[2][0] = sD[j + 1][lm], v[2][1] = sD[j + 1][col], v[2][2] = sD[j + 1][lp];
+        } else {
+          const int y = y0 - H + j;
+          const int jm = (!pery && y == 0) ? j : j - 1, jp = (!pery && y == ny - 1) ? j : j + 1;
+          v[0][0] = sD[jm][lm], v[0][1] = sD[jm][col], v[0][2] = sD[jm][lp];
+          v[2][0] = sD[jp][lm], v[2][1] = sD[jp][col], v[2][2] = sD[jp][lp];
+        }
         T gx_, gy_;
         grad_c(v, gx_, gy_);
         T u[8], s8[8];
@@ -533,9 +568,38 @@ __global__ __launch_bounds__((kWave * sweepn_waves<T, SHIFT, APPS + RES, ALT>())
       const int y = y0 - H + j;
       const int c = j - 1;
       const int lc = pl ? col : 4;  // keep LDS indices in range on idle lanes
+      bool wl = false, wr = false, wb = false, wt = false;
+      if (bnd) {
+        const bool yreal = pery ? (y >= -H && y < ny + H) : (y >= 0 && y < ny);
+        const bool real = pl && xreal && yreal;
+        wl = real && !perx && x == 0;
+        wr = real && !perx && x == nx - 1;
+        wb = real && !pery && y == 0;
+        wt = real && !pery && y == ny - 1;
+      }
+      // the value a population arrives from: the neighbour's, at a symmetry
+      // wall the mirror image (own column or row), at a halfway rule and where
+      // two walls meet this cell's opposite population
       T gi[8];
+      const T* sp = &sS[0][c][lc];
+      if (!bnd) {
 #pragma unroll
-      for (int q = 0; q < 8; ++q) gi[q] = sS[q][c - cy8(q)][lc - cx8(q)];
+        for (int q = 0; q < 8; ++q) gi[q] = sp[q * PS - cy8(q) * RX - cx8(q)];
+      } else {
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+          const int cx = cx8(q), cy = cy8(q), back = opp8(q) * PS;
+          int off = q * PS - cy * RX - cx;
+          const int offx = (cx > 0 ? symL : symR) ? mx8(q) * PS - cy * RX : back;
+          const int offy = (cy > 0 ? symB : symT) ? my8(q) * PS - cx : back;
+          const bool ox = cx > 0 ? wl : wr, oy = cy > 0 ? wb : wt;
+          if (cx != 0 && cy != 0)
+            off = ox ? (oy ? back : offx) : (oy ? offy : off);
+          else
+            off = cx != 0 ? (ox ? offx : off) : (oy ? offy : off);
+          gi[q] = sp[off];
+        }
+      }
       // own reference, read from LDS where a rule needs it (FP64 registers
       // per row would cost occupancy)
       auto own_x = [&]() { return r64 ? sEd[0][j][col] : double(sEf[0][j][col]); };
@@ -567,93 +631,60 @@ __global__ __launch_bounds__((kWave * sweepn_waves<T, SHIFT, APPS + RES, ALT>())
           Cr[kk][6] = T(-twelfth * (sEf[2][j + 1][lc + 1] - sp));
           Cr[kk][7] = T(-twelfth * (sEf[3][j + 1][lc - 1] - sm));
         }
+        if (app == 0 && bnd && (wl || wr || wb || wt)) {
+          // wall populations: the source's reference in the population it is
+          // read from minus this cell's (mirrors flip the component normal to
+          // the wall, a halfway rule both), a halfway rule's data, and no
+          // reference at all in a traction rule; once per launch
+          using Rf = std::conditional_t<R64, double, float>;
+          auto rx = [&](int jj, int ll) { return r64 ? Rf(sEd[0][jj][ll]) : Rf(sEf[0][jj][ll]); };
+          auto ry = [&](int jj, int ll) { return r64 ? Rf(sEd[1][jj][ll]) : Rf(sEf[1][jj][ll]); };
+          const Rf ex = rx(j, lc), ey = ry(j, lc);
 #pragma unroll
-        for (int q = 0; q < 8; ++q) gi[q] += sc * Cr[kk][q];
+          for (int q = 0; q < 8; ++q) {
+            const int cx = cx8(q), cy = cy8(q);
+            const bool ox = (cx > 0 && wl) || (cx < 0 && wr), oy = (cy > 0 && wb) || (cy < 0 && wt);
+            if (!(ox || oy)) continue;
+            const bool hx = ox && !(cx > 0 ? symL : symR), hy = oy && !(cy > 0 ? symB : symT);
+            if (hx || hy) {
+              const int type = hy ? (cy > 0 ? elB : elT) : (cx > 0 ? elL : elR);
+              const int my_ = cy > 0 ? (q == 1 ? 0 : q - 3) : (q == 3 ? 0 : q - 5);
+              const int mx_ = cx > 0 ? (q == 0 ? 0 : (q - 1) / 3) : (q == 2 ? 0 : q - 4);
+              const Rf add = FINE ? Rf(hy ? sBy[cy > 0 ? 0 : 1][cy != 0 ? my_ : 0][FINE ? lc : 0]
+                                          : sBx[cx > 0 ? 0 : 1][cx != 0 ? mx_ : 0][FINE ? j : 0])
+                                  : Rf(0);
+              Cr[kk][q] = T(type == kElDirichlet ? add - Rf(2) * el_geq<Rf>(q, ex, ey) : add);
+            } else {
+              const int jj = oy ? j : j - cy, ll = ox ? lc : lc - cx;
+              const Rf sx = rx(jj, ll), sy = ry(jj, ll);
+              Cr[kk][q] = T(el_geq<Rf>(q, ox ? -sx : sx, oy ? -sy : sy) - el_geq<Rf>(q, ex, ey));
+            }
+          }
+        }
       }
-      // the reference of a neighbour (wall rules), in FP64
-      auto rx = [&](int jj, int ll) { return r64 ? sEd[0][jj][ll] : double(sEf[0][jj][ll]); };
-      auto ry = [&](int jj, int ll) { return r64 ? sEd[1][jj][ll] : double(sEf[1][jj][ll]); };
-      bool wl = false, wr = false, wb = false, wt = false;
-      int gy = 0;
-      if (bnd) {
-        const bool yreal = pery ? (y >= -H && y < ny + H) : (y >= 0 && y < ny);
-        const bool real = pl && xreal && yreal;
-        gy = ghost_map(clampi(y, -H, ny + H - 1), ny, pery);
-        wl = real && !perx && x == 0;
-        wr = real && !perx && x == nx - 1;
-        wb = real && !pery && y == 0;
-        wt = real && !pery && y == ny - 1;
-      }
-      if (bnd && (wl || wr || wb || wt)) {
-        // wall terms against the reference: FP64 with FP64 references, else in
-        // the population precision
-        const double ex = SHIFT ? own_x() : 0.0, ey = SHIFT ? own_y() : 0.0;
-        const T ext = T(ex), eyt = T(ey);
-        // mirror rules: the source's reference (population qm) minus this
-        // cell's (population qq); bounce-back rules: twice this cell's
-        auto mirror = [&](int qm, int qq, int jj, int ll) -> T {
-          if (r64) return T(el_geq<double>(qm, rx(jj, ll), ry(jj, ll)) - el_geq<double>(qq, ex, ey));
-          return el_geq<T>(qm, T(rx(jj, ll)), T(ry(jj, ll))) - el_geq<T>(qq, ext, eyt);
-        };
-        auto twice_own = [&](int qq) -> T {
-          return r64 ? T(2.0 * el_geq<double>(qq, ex, ey)) : T(2) * el_geq<T>(qq, ext, eyt);
-        };
+      if (half) {
+        // the halfway rules' sign and (unshifted storage) data; where two
+        // walls meet the bottom or top wall's rule wins, unless it mirrors
 #pragma unroll
         for (int q = 0; q < 8; ++q) {
           const int cx = cx8(q), cy = cy8(q);
-          const bool ox = (cx > 0 && wl) || (cx < 0 && wr);
-          const bool oy = (cy > 0 && wb) || (cy < 0 && wt);
-          if (!(ox || oy)) continue;
-          const int elx = cx > 0 ? P.el[kLeft] : P.el[kRight];
-          const int ely = cy > 0 ? P.el[kBottom] : P.el[kTop];
-          T v = T(0);
-          bool usex = false, half = false;
-          if (ox && oy) {
-            if (elx == kElSymmetry && ely == kElSymmetry) {
-              v = sS[opp8(q)][c][lc];
-              if (SHIFT) v -= sc * twice_own(q);
-            } else {
-              usex = ely == kElSymmetry;
-              half = true;
-            }
-          } else if (ox) {
-            usex = true;
-            if (elx == kElSymmetry) {
-              v = sS[mx8(q)][c - cy][lc];
-              if (SHIFT) v += sc * mirror(mx8(q), q, j - cy, lc);
-            } else {
-              half = true;
-            }
-          } else {
-            if (ely == kElSymmetry) {
-              v = sS[my8(q)][c][lc - cx];
-              if (SHIFT) v += sc * mirror(my8(q), q, j, lc - cx);
-            } else {
-              half = true;
-            }
+          const bool hx = (cx > 0 && wl && !symL) || (cx < 0 && wr && !symR);
+          const bool hy = (cy > 0 && wb && !symB) || (cy < 0 && wt && !symT);
+          const bool neg = hy ? (cy > 0 ? elB : elT) == kElTraction : (hx && (cx > 0 ? elL : elR) == kElTraction);
+          gi[q] = neg ? -gi[q] : gi[q];
+          if (FINE && !SHIFT) {
+            const int my_ = cy > 0 ? (q == 1 ? 0 : q - 3) : (q == 3 ? 0 : q - 5);
+            const int mx_ = cx > 0 ? (q == 0 ? 0 : (q - 1) / 3) : (q == 2 ? 0 : q - 4);
+            T add = T(0);
+            if (cx != 0) add = hx ? T(sBx[cx > 0 ? 0 : 1][cx != 0 ? mx_ : 0][FINE ? j : 0]) : add;
+            if (cy != 0) add = hy ? T(sBy[cy > 0 ? 0 : 1][cy != 0 ? my_ : 0][FINE ? lc : 0]) : add;
+            gi[q] += sc * add;
           }
-          if (half) {
-            const int type = usex ? elx : ely;
-            const double* bc = FINE ? (usex ? (cx > 0 ? P.elbc[kLeft] : P.elbc[kRight])
-                                            : (cy > 0 ? P.elbc[kBottom] : P.elbc[kTop]))
-                                    : nullptr;
-            const int bidx = usex ? gy : gx;
-            const T o = sS[opp8(q)][c][lc];
-            if (SHIFT && r64 && type == kElDirichlet) {
-              // the wall term and the reference's share in FP64, rounded once
-              v = o + sc * T((bc ? bc[8 * bidx + q] : 0.0) - 2.0 * el_geq<double>(q, ex, ey));
-            } else {
-              const T add = bc ? sc * T(bc[8 * bidx + q]) : T(0);
-              if (type == kElDirichlet) {
-                v = o + add;
-                if (SHIFT) v -= sc * twice_own(q);
-              } else {
-                v = -o + add;
-              }
-            }
-          }
-          gi[q] = v;
         }
+      }
+      if (SHIFT) {
+#pragma unroll
+        for (int q = 0; q < 8; ++q) gi[q] += sc * Cr[kk][q];
       }
       const bool out = pl && x >= 0 && x < nx && y >= 0 && y < ny && col >= H && col < RX - H &&
                        j >= H && j < RR - H;

@@ -1,0 +1,65 @@
+"""GPU test of the wall rules in the launches of several applications: every
+meeting of two wall types at a corner and beside periodic sides, with random
+boundary data, against the FP64 oracle, at sizes where a wall falls on, next to
+and a tile's remainder away from a tile edge."""
+import sys
+
+import numpy as np
+import pytest
+
+from conftest import oracle_threads
+from gpu_helpers import rel
+from oracle.oracle import Oracle
+from paper_2409_11382_amd import problem as P
+
+pytestmark = pytest.mark.gpu
+
+BIG = 1 << 40
+EL = {"P": P.EL_PERIODIC, "D": P.EL_DIRICHLET, "T": P.EL_TRACTION, "S": P.EL_SYMMETRY}
+FLOW = {"P": P.FLOW_PERIODIC, "D": P.FLOW_NOFLOW, "T": P.FLOW_DIRICHLET, "S": P.FLOW_SYMMETRY}
+
+
+@pytest.fixture(scope="module")
+def lbm():
+    import torch
+
+    assert torch.cuda.is_available(), "GPU tests need a GPU"
+    from paper_2409_11382_amd import lbm as L
+
+    L.load_library()
+    return L
+
+
+def _problem(walls, nx, ny):
+    """walls: types of left, right, bottom, top; random displacements,
+    tractions and pressures on them, uniform permeability"""
+    lam, mu = P.plane_stress_lame(1.0, 0.3)
+    sides = [P.Side.uniform(ny if k < 2 else nx, EL[c], FLOW[c]) for k, c in enumerate(walls)]
+    h = 1.0 / max(nx, ny)
+    p = P.Problem(nx=nx, ny=ny, dx=h, dt=h * h / 4, lam=lam, mu=mu, c0=1.0, alpha=0.8, kappa=1.0, sides=sides,
+                  K=4, ne_fixed=2, name="walls_" + walls)
+    return P.with_random_boundary_data(p, seed=11, scale=1e-2)
+
+
+@pytest.mark.parametrize("walls", ["DTSD", "SDTS", "TSDT", "SSDT", "DDTT", "TDSS", "PPDT", "PPSS", "TDPP", "SSPP"])
+@pytest.mark.parametrize("nx,ny", [(112, 48), (58, 50)])
+def test_wall_types_in_multi_application_launches(lbm, walls, nx, ny):
+    p = _problem(walls, nx, ny)
+    o = Oracle(p, threads=oracle_threads())
+    o.step(2)
+    B = o.fields()
+    pairs = dict(quad_max_cells=0, tall_max_cells=0)
+    for prec, tol in (("fp64", 1e-10), ("fp32_shifted", 1e-5)):
+        for bounds in (pairs, dict(quad_max_cells=0, tall_max_cells=BIG), dict(quad_max_cells=BIG),
+                       dict(quad_max_cells=BIG, quad_res_narrow_max_cells=0)):
+            s = lbm.Solver(p, prec)
+            s.set_tuning(bounds)
+            s.step(2)
+            A = s.fields()
+            s.close()
+            e = {k: rel(A[k], B[k]) for k in ("eta", "p")}
+            print(walls, nx, ny, prec, bounds, e, flush=True)
+            sys.stdout.flush()
+            assert max(e.values()) <= tol  # no data on periodic and symmetry sides: the fields stay zero there
+            if prec == "fp64":
+                assert float(np.abs(A["eta"] - B["eta"]).max()) <= tol * float(np.abs(B["eta"]).max())
