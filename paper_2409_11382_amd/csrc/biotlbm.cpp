@@ -453,6 +453,12 @@ bp_status upload_loads(hipStream_t st, Prob& P, const double* body_f, const doub
   return BP_OK;
 }
 
+void set_tiles_x(LevelD& v, int A, int tiles) {
+  v.tiles_xn[A] = tiles;
+  v.tile_shift[A] = 0;
+  while ((1 << v.tile_shift[A]) < tiles) ++v.tile_shift[A];
+}
+
 // set up one problem inside device memory at `base` (layout lo already made)
 bp_status setup_problem(const bp_problem* p, const Layout& lo, char* base, hipStream_t st, Prob& P) {
   P.lo = lo;
@@ -479,7 +485,7 @@ bp_status setup_problem(const bp_problem* p, const Layout& lo, char* base, hipSt
     d.lv[l].ny = v.ny;
     d.lv[l].pitch = v.pitch;
     d.lv[l].tiles_x = sweep_tiles_x(v.nx);
-    for (int A = 2; A <= 5; ++A) d.lv[l].tiles_xn[A] = sweepn_tiles_x(v.nx, A, false);  // A = 5: set per depth
+    for (int A = 2; A <= 5; ++A) set_tiles_x(d.lv[l], A, sweepn_tiles_x(v.nx, A, false));  // A = 5: set per depth
     d.lv[l].dbl = v.dbl ? 1 : 0;
     d.lv[l].plane = v.plane;
   }
@@ -722,7 +728,8 @@ struct Engine {
   // deepest point of the cycle when the tails start at several depths
   bool merge_tails = true;
   int tail_all_off = 0, tail_all_cnt = 0, tail_depths = 0;
-  bool fuse = true;  // two-application sweeps in the fixed-cycle schedule
+  bool want_fuse = true;  // several applications per launch in the time-step schedule
+  bool fuse = true;       // the same where every plane fits the launches' 32-bit offsets
   bool quad = true;  // four-application sweeps on small coarse levels
   // launch-shape bounds (cells a depth covers in all); bp_tuning
   int64_t quad_max_cells = kQuadMaxCells;
@@ -776,9 +783,13 @@ bp_status engine_upload(Engine& E) {
   for (size_t i = 0; i < np; ++i) pd[i] = E.probs[i]->d;
   E.maxL = 1;
   E.ref64 = false;
+  E.fuse = E.want_fuse;
   for (auto* P : E.probs) {
     E.maxL = std::max(E.maxL, P->L);
     E.ref64 = E.ref64 || (P->lo.shift && P->lo.ref64);
+    // the multi-application launches address a plane by 32-bit byte offsets
+    const int64_t size = (P->lo.fdbl || (P->lo.shift && P->lo.ref64)) ? 8 : 4;
+    if (P->lo.plane * size >= int64_t(1) << 32) E.fuse = false;
   }
   std::vector<int2> tiles;
   E.depth.assign(E.maxL, DepthLists());
@@ -795,7 +806,7 @@ bp_status engine_upload(Engine& E) {
     E.depth[d].tall = depth_cells <= E.tall_max_cells;
     for (size_t i = 0; i < np; ++i) {  // tiles along x of the level at this depth, by its A = 5 width
       const int l = E.probs[i]->L - d;
-      if (l >= 1) pd[i].lv[l].tiles_xn[5] = sweepn_tiles_x(E.probs[i]->lo.lv[l].nx, 5, alt_at(E, d, 5));
+      if (l >= 1) set_tiles_x(pd[i].lv[l], 5, sweepn_tiles_x(E.probs[i]->lo.lv[l].nx, 5, alt_at(E, d, 5)));
     }
     for (int set = 0; set < 8; ++set)
       for (int g = 0; g < 3; ++g) {
@@ -810,7 +821,11 @@ bp_status engine_upload(Engine& E) {
           const int A = set_apps(set);
           const int nt = set >= kSetFused ? sweepn_tiles(v.nx, v.ny, v.dbl, A, E.shift && d == 0, alt_at(E, d, A))
                                           : sweep_tiles(v.nx, v.ny);
-          for (int t = 0; t < nt; ++t) tiles.push_back(make_int2((int)i, t));
+          // multi-application launches take the tile's column and row packed
+          const LevelD& D = pd[i].lv[l];
+          for (int t = 0; t < nt; ++t)
+            tiles.push_back(make_int2(
+                (int)i, set >= kSetFused ? (t / D.tiles_xn[A] << D.tile_shift[A] | t % D.tiles_xn[A]) : t));
         }
         if (E.xcd_order) xcd_order(tiles, E.depth[d].off[set][g]);
         E.depth[d].cnt[set][g] = (int)tiles.size() - E.depth[d].off[set][g];
@@ -1291,7 +1306,7 @@ bp_status engine_init(Engine& E, char* area, size_t area_bytes, size_t probs_cap
   if (const char* e = std::getenv("BIOT_NO_GRAPH")) E.use_graph = (std::atoi(e) == 0);
   if (const char* e = std::getenv("BIOT_NO_XCD_ORDER")) E.xcd_order = (std::atoi(e) == 0);
   if (const char* e = std::getenv("BIOT_NO_MERGE_TAIL")) E.merge_tails = (std::atoi(e) == 0);
-  if (const char* e = std::getenv("BIOT_NO_FUSE")) E.fuse = (std::atoi(e) == 0);
+  if (const char* e = std::getenv("BIOT_NO_FUSE")) E.want_fuse = (std::atoi(e) == 0);
   if (const char* e = std::getenv("BIOT_NO_QUAD")) E.quad = (std::atoi(e) == 0);
   if (const char* e = std::getenv("BIOT_QUAD_MAX_CELLS")) E.quad_max_cells = std::atoll(e);
   if (const char* e = std::getenv("BIOT_TALL_MAX_CELLS")) E.tall_max_cells = std::atoll(e);
@@ -2149,7 +2164,7 @@ bp_status create_solver(const bp_problem* p, const Layout& lo, char* w, void* hi
                              p->cycle, no_alloc);
   s->E.csweeps = p->coarse_sweeps;
   s->E.lag = p->lag != 0;
-  if (s->E.lag) s->E.fuse = false;  // the lag runs single applications
+  if (s->E.lag) s->E.want_fuse = false;  // the lag runs single applications
   if (rc == BP_OK) rc = setup_problem(p, lo, w, st, s->P);
   if (rc == BP_OK) {
     s->E.probs = {&s->P};

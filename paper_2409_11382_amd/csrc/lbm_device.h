@@ -48,6 +48,28 @@ __device__ __forceinline__ int ghost_map(int i, int n, bool periodic) {
   return i < 0 ? -i - 1 : 2 * n - 1 - i;
 }
 
+// the same for an index at most `reach` < n outside its range by one wrap (no
+// division); smaller ranges take the general form
+__device__ __forceinline__ int wrap_index(int i, int n, int reach) {
+  if (n < reach) return ghost_map(i, n, true);  // uniform
+  return i < 0 ? i + n : (i >= n ? i - n : i);
+}
+
+// ------------------------------------------------------------- global memory
+// pointers known to be global (descriptors hold them, so the compiler cannot
+// tell and would take flat instructions), addressed by a scalar base and a
+// 32-bit byte offset per lane
+template <typename T> using GPtr = __attribute__((address_space(1))) T*;
+template <typename T> __device__ __forceinline__ GPtr<T> gptr(const void* p) {
+  return (GPtr<T>)(uintptr_t)p;
+}
+template <typename T> __device__ __forceinline__ T gload(GPtr<T> base, uint32_t off) {
+  return *(GPtr<T>)((GPtr<char>)base + off);
+}
+template <typename T> __device__ __forceinline__ void gstore(GPtr<T> base, uint32_t off, T v) {
+  *(GPtr<T>)((GPtr<char>)base + off) = v;
+}
+
 // --------------------------------------------------------------- constants
 template <typename T> struct ElConst {
   T om_s, om_d;      // relaxation rates of m_s and of m_d, m_11 (Table 2)

@@ -28,6 +28,7 @@ struct LevelD {
   int nx, ny, pitch;
   int tiles_x;       // sweep tiles along x: ceil(nx / kTileX)
   int tiles_xn[6];   // multi-application sweep tiles along x, by applications per launch (2..5)
+  int tile_shift[6]; // their entries hold tile row << shift | tile column
   int dbl;           // FP64 storage
   int64_t plane;
 };
