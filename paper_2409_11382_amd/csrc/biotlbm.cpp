@@ -153,6 +153,8 @@ struct Layout {
   bool lag = false;
   int ntiles_fine = 0, ntiles_fine2 = 0;
   int tail_depth = 0;  // depth of the coarse tail's top level (0: no tail)
+  int tml = 0;         // the tail's levels that are one matrix (tml..1; 0: none)
+  size_t off_tmat = SIZE_MAX;
   size_t total = 0;
 };
 
@@ -249,6 +251,12 @@ void make_layout(const bp_problem* p, Layout& lo) {
   if (lo.tail_depth > 0)
     for (int l = 1; l <= (lo.full_tail ? lo.L : lo.L - lo.tail_depth); ++l) tcells += (size_t)lo.lv[l].nx * lo.lv[l].ny;
   lo.off_ttab = take(tcells * 8 * sizeof(uint32_t));
+  // the tail's smallest levels as one matrix (V-cycles)
+  lo.tml = 0;
+  if (lo.tail_depth > 0 && (lo.cycle == BP_CYCLE_V || lo.cycle == BP_CYCLE_FMG))
+    for (int l = 1; l <= std::min(lo.L - lo.tail_depth, kTailDenseLevels); ++l)
+      if (lo.lv[l].nx * lo.lv[l].ny <= kTailDenseCells) lo.tml = l;
+  if (lo.tml > 0) lo.off_tmat = take(tail_matrix_bytes(lo.lv[lo.tml].nx * lo.lv[lo.tml].ny));
   lo.off_addt = lo.full_tail ? take(8 * lo.plane * fs) : SIZE_MAX;
   for (int s = 0; s < 4; ++s) {
     const int n = side_len(s, p->nx, p->ny);
@@ -483,6 +491,7 @@ bp_status setup_problem(const bp_problem* p, const Layout& lo, char* base, hipSt
     d.lv[l].r = v.oR == SIZE_MAX ? nullptr : (void*)(base + v.oR);
     d.lv[l].nx = v.nx;
     d.lv[l].ny = v.ny;
+    d.lv[l].inv_nx = ((1u << 20) + (uint32_t)v.nx - 1) / (uint32_t)v.nx;
     d.lv[l].pitch = v.pitch;
     d.lv[l].tiles_x = sweep_tiles_x(v.nx);
     for (int A = 2; A <= 5; ++A) set_tiles_x(d.lv[l], A, sweepn_tiles_x(v.nx, A, false));  // A = 5: set per depth
@@ -538,6 +547,12 @@ bp_status setup_problem(const bp_problem* p, const Layout& lo, char* base, hipSt
       HIPCHK(launch_tail_tables(d.el, lo.lv[l].nx, lo.lv[l].ny, d.ttab + o, st));
       o += (size_t)8 * lo.lv[l].nx * lo.lv[l].ny;
     }
+  }
+  d.tml = lo.tml;
+  if (lo.tml > 0) {
+    double* m = (double*)(base + lo.off_tmat);
+    HIPCHK(launch_tail_matrix(d, lo.tml, p->K, m, st));
+    d.tmat = m;
   }
 
   // permeability -> lattice relaxation rate of the flow LBM (eq. pressure:rate)
@@ -1880,7 +1895,7 @@ std::string op_name(const Op& o) {
 // by the process until it ends.  In host code `scratch` names a host-side
 // stand-in, never a device address: the device address comes from
 // hipGetSymbolAddress, once per device with that device current.
-constexpr size_t kScratchBytes = size_t(64) << 20;
+constexpr size_t kScratchBytes = (size_t(64) << 20) + tail_matrix_bytes(kTailDenseCells);  // 64 MiB, and a coarse matrix
 static __device__ __align__(256) char scratch[kScratchBytes];
 constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mu;

@@ -26,6 +26,7 @@ struct LevelD {
   void* gB;          // population buffer B
   void* r;           // coarse right-hand side (8 planes), null on the finest level
   int nx, ny, pitch;
+  uint32_t inv_nx;   // ceil(2^20 / nx): rows of cells below 1024 without a division
   int tiles_x;       // sweep tiles along x: ceil(nx / kTileX)
   int tiles_xn[6];   // multi-application sweep tiles along x, by applications per launch (2..5)
   int tile_shift[6]; // their entries hold tile row << shift | tile column
@@ -68,6 +69,8 @@ struct ProbD {
   int grad_central;           // explicit force: central difference of p instead of first moments
   int ntiles_fine2;           // tiles of the finest level's last post-smoothing launch (multi-application)
   int ntiles_test;            // tiles of the finest level's first pre-smoothing launch (the adaptive test)
+  const double* tmat;         // coarse tail: the V-cycle of levels tml..1 from zero as a matrix (or null)
+  int tml;                    // its top level, 0: none
   uint32_t* ttab;             // coarse tail: per-cell gather tables of levels 1.. (8 words per cell)
   void* addt;                 // whole-problem tail: the finest level's wall terms, 8 planes
                               // in the population precision (or null)
@@ -136,6 +139,11 @@ constexpr int kTailThreads = 1024;
 constexpr int kTailCellsF32 = 1024;   // largest tail level (cells) in FP32 storage
 constexpr int kTailCellsF64 = 1024;   // and in FP64 storage
 constexpr int kTailLdsBytes = 9 * kTailCellsF64 * 8;
+// a V-cycle's levels of at most this many cells (and so many levels) are one
+// matrix: at 16 cells it is 128 KiB, read by one compute unit in under a
+// microsecond where the sweeps of 4^2 and 2^2 take 12; 25 cells would already
+// need 313 KiB against one level's sweeps
+constexpr int kTailDenseCells = 16, kTailDenseLevels = 5;
 struct TailL {
   const ProbD* probs;
   const int* pids;
@@ -243,6 +251,10 @@ hipError_t launch_tail(const TailL& a, int nprobs, bool dbl, hipStream_t s);
 // gather tables of one coarse-tail level (nx * ny <= kTailThreads) for the
 // elastic side types el[4]
 hipError_t launch_tail_tables(const int* el, int nx, int ny, uint32_t* out, hipStream_t s);
+// the matrix of the V-cycle of levels top..1 from zero (K smoothing steps),
+// tail_matrix_bytes(cells of level top) bytes at out
+hipError_t launch_tail_matrix(const ProbD& P, int top, int K, double* out, hipStream_t s);
+constexpr size_t tail_matrix_bytes(int cells) { return (size_t)cells * kTailThreads * sizeof(double); }
 hipError_t launch_finalize(const ProbL& a, int nprobs, hipStream_t s);
 // adaptive cycles on the device: reset the stop flag and count for a step
 // (the stopping test itself follows the norms in k_finalize)

@@ -1492,6 +1492,34 @@ __device__ __forceinline__ void tail_relax(const ElConst<T>& k, int n, const Tai
   }
 }
 
+// the first smoothing application of a zero iterate: D(g) = 0, so the
+// collision of -R needs no neighbour.  One barrier; sG is read until the next.
+template <typename T>
+__device__ __forceinline__ void tail_first(const ElConst<T>& k, int n, const TailTab (&tb)[1], T (&G)[1][8],
+                                           const T (&R)[1][8], T* sG) {
+  const int c = threadIdx.x;
+  if (c < n) {
+    T u[8], s8[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) u[q] = -R[0][q];
+    el_collide(u, T(0), T(0), k, s8, k.gamma);
+#pragma unroll
+    for (int q = 0; q < 8; ++q) sG[q * n + c] = s8[q];
+  }
+  __syncthreads();
+  if (c < n) {
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      const uint32_t code = (q & 1) ? hi16(tb[0].pl[q >> 1]) : lo16(tb[0].pl[q >> 1]);
+      const T v = sG[code & 0x7fffu];
+      G[0][q] = (code & 0x8000u) ? -v : v;
+    }
+  } else {
+#pragma unroll
+    for (int q = 0; q < 8; ++q) G[0][q] = T(0);
+  }
+}
+
 // the gather tables of level l (built once at setup by k_tail_tables)
 __device__ __forceinline__ const uint4* tail_tab_ptr(const ProbD& P, int l) {
   size_t o = 0;
@@ -1531,21 +1559,33 @@ hipError_t launch_tail_tables(const int* el, int nx, int ny, uint32_t* out, hipS
   return hipGetLastError();
 }
 
-// one thread, one cell (c < n): the 8 planes of a level buffer
+// row of cell c < 1024 in a level of nx columns, inv = ceil(2^20 / nx): exact,
+// since c (inv nx - 2^20) < 1024 nx and the quotient's fraction is below
+// 1 - 1/nx
+__device__ __forceinline__ int tail_row(int c, uint32_t inv) { return (int)(((uint32_t)c * inv) >> 20); }
+
+// one thread, one cell (c < n): the 8 planes of a level buffer (waves without
+// a cell load nothing)
 template <typename T>
 __device__ __forceinline__ void tail_load1(const LevelD& V, const void* buf, int c, T (&A)[1][8]) {
-  const bool in = c < V.nx * V.ny;
-  const int64_t idx = in ? (int64_t)(c / V.nx) * V.pitch + c % V.nx : 0;
 #pragma unroll
-  for (int q = 0; q < 8; ++q) A[0][q] = in ? ((const T*)buf)[q * V.plane + idx] : T(0);
+  for (int q = 0; q < 8; ++q) A[0][q] = T(0);
+  if (c >= V.nx * V.ny) return;
+  const int y = tail_row(c, V.inv_nx);
+  const uint32_t off = (uint32_t)(y * (V.pitch - V.nx) + c) * (uint32_t)sizeof(T);
+  const GPtr<T> p = gptr<T>(buf);
+#pragma unroll
+  for (int q = 0; q < 8; ++q) A[0][q] = gload(p + q * V.plane, off);
 }
 
 template <typename T>
 __device__ __forceinline__ void tail_store1(const LevelD& V, void* buf, int c, const T (&A)[1][8]) {
   if (c >= V.nx * V.ny) return;
-  const int64_t idx = (int64_t)(c / V.nx) * V.pitch + c % V.nx;
+  const int y = tail_row(c, V.inv_nx);
+  const uint32_t off = (uint32_t)(y * (V.pitch - V.nx) + c) * (uint32_t)sizeof(T);
+  const GPtr<T> p = gptr<T>(buf);
 #pragma unroll
-  for (int q = 0; q < 8; ++q) ((T*)buf)[q * V.plane + idx] = A[0][q];
+  for (int q = 0; q < 8; ++q) gstore(p + q * V.plane, off, A[0][q]);
 }
 
 template <typename T>
@@ -1554,41 +1594,171 @@ __device__ __forceinline__ void tail_zero(T (&A)[1][8]) {
   for (int q = 0; q < 8; ++q) A[0][q] = T(0);
 }
 
+// ---- the smallest levels as one matrix.  A V-cycle from a zero iterate on
+// levels of at most kTailDenseCells cells is a fixed linear map of its
+// right-hand side, and its 17 sweeps of one wave each (two levels, K = 4) are
+// a chain of about 12 us, while the map's 128 x 128 matrix is read in under
+// one.  It is formed once per problem in FP64 (k_tail_matrix) and applied in
+// FP64 to the right-hand side as the sweeps would receive it.  Measured, tail
+// of a 512^2 problem: 46.1 -> 33.3 us in FP32, 61 -> 45 in FP64 (with row
+// numbers by multiplication and first sweeps without a D exchange).
+constexpr int kTailPart = 8;  // threads per row of the matrix
+
+// G = V-cycle on levels l..1 (at most kTailDenseCells cells each) from zero
+// with the right-hand side R, in FP64 registers; rows of the recursion are
+// kept in `keep` (LDS), 16 planes per level
+__device__ __forceinline__ void tail_small(const ProbD& P, int top, int K, const double (&R0)[1][8], double (&G)[1][8],
+                                           double* keep, double* lds) {
+  const int c = threadIdx.x;
+  const ElConst<double> k = tail_consts<double>(P);
+  TailTab tb[1];
+  double R[1][8];
+#pragma unroll
+  for (int q = 0; q < 8; ++q) R[0][q] = R0[0][q];
+  constexpr int N = kTailDenseCells;
+  for (int l = top; l >= 1; --l) {
+    const LevelD& V = P.lv[l];
+    const int nx = V.nx, n = nx * V.ny;
+    double *sD = lds, *sG = lds + n;
+    tail_tab_load(P, l, c, tb);
+    tail_zero(G);
+    const int sweeps = l > 1 ? K : P.csweeps;
+    for (int s = 0; s < sweeps; ++s) tail_relax<double, 1>(k, n, tb, G, R, sD, sG, true);
+    if (l == 1) break;
+    if (c < n) {
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        keep[(16 * l + q) * N + c] = G[0][q];
+        keep[(16 * l + 8 + q) * N + c] = R[0][q];
+      }
+    }
+    tail_relax<double, 1>(k, n, tb, G, R, sD, sG, false);
+    __syncthreads();
+    if (c < n) {
+#pragma unroll
+      for (int q = 0; q < 8; ++q) sG[q * n + c] = G[0][q];
+    }
+    __syncthreads();
+    const LevelD& C = P.lv[l - 1];
+    const int cnx = C.nx, f0 = 2 * c + 2 * cnx * tail_row(c, C.inv_nx), f1 = f0 + nx;
+#pragma unroll
+    for (int q = 0; q < 8; ++q)
+      R[0][q] = c < cnx * C.ny ? (sG[q * n + f0] + sG[q * n + f0 + 1]) + (sG[q * n + f1] + sG[q * n + f1 + 1]) : 0.0;
+    __syncthreads();
+  }
+  for (int l = 2; l <= top; ++l) {
+    const LevelD& V = P.lv[l];
+    const int nx = V.nx, n = nx * V.ny, cnx = nx / 2, cn = cnx * (V.ny / 2);
+    double *sD = lds, *sG = lds + n;
+    __syncthreads();
+    if (c < cn) {
+#pragma unroll
+      for (int q = 0; q < 8; ++q) sG[q * cn + c] = G[0][q];
+    }
+    __syncthreads();
+    const int y = tail_row(c, V.inv_nx), ci = (y >> 1) * cnx + ((c - y * nx) >> 1);
+    if (c < n) {
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        G[0][q] = keep[(16 * l + q) * N + c] + sG[q * cn + ci];
+        R[0][q] = keep[(16 * l + 8 + q) * N + c];
+      }
+    }
+    __syncthreads();
+    tail_tab_load(P, l, c, tb);
+    for (int s = 0; s < K; ++s) tail_relax<double, 1>(k, n, tb, G, R, sD, sG, true);
+  }
+}
+
+// one block per unit right-hand side: column b = q n + c of the matrix, stored
+// so that thread t of the tail reads its entries k at out[k 1024 + t]
+__global__ __launch_bounds__(kWave) void k_tail_matrix(ProbD P, int top, int K, double* out) {
+  constexpr int N = kTailDenseCells;
+  __shared__ double lds[9 * N], keep[16 * (kTailDenseLevels + 1) * N];
+  const int c = threadIdx.x, n = P.lv[top].nx * P.lv[top].ny, b = blockIdx.x;
+  double R[1][8], G[1][8];
+#pragma unroll
+  for (int q = 0; q < 8; ++q) R[0][q] = (q * n + c == b && c < n) ? 1.0 : 0.0;
+  tail_small(P, top, K, R, G, keep, lds);
+  if (c < n) {
+#pragma unroll
+    for (int q = 0; q < 8; ++q) out[(b / kTailPart) * kTailThreads + (q * n + c) * kTailPart + b % kTailPart] = G[0][q];
+  }
+}
+
+hipError_t launch_tail_matrix(const ProbD& P, int top, int K, double* out, hipStream_t s) {
+  const int n = P.lv[top].nx * P.lv[top].ny;
+  if (top < 1 || top > kTailDenseLevels || n > kTailDenseCells) return hipErrorInvalidValue;
+  hipLaunchKernelGGL(k_tail_matrix, dim3(8 * n), dim3(kWave), 0, s, P, top, K, out);
+  return hipGetLastError();
+}
+
+// the matrix times the right-hand side R of level P.tml (thread c: cell c),
+// left in LDS as plane q of cell c at lds + n + q n in type TT
+template <typename TR, typename TT>
+__device__ __forceinline__ void tail_dense(const ProbD& P, const TR (&R)[1][8], char* lds) {
+  const int t = threadIdx.x, n = P.lv[P.tml].nx * P.lv[P.tml].ny, n8 = 8 * n;
+  const GPtr<double> M = gptr<double>(P.tmat);
+  constexpr int KM = 8 * kTailDenseCells / kTailPart;
+  double m[KM];
+#pragma unroll
+  for (int k = 0; k < KM; ++k) m[k] = k * kTailPart < n8 ? gload(M + k * kTailThreads, (uint32_t)t * 8u) : 0.0;
+  double* r = (double*)lds;
+  if (t < n) {
+#pragma unroll
+    for (int q = 0; q < 8; ++q) r[q * n + t] = double(R[0][q]);
+  }
+  __syncthreads();
+  const int part = t % kTailPart, o = t / kTailPart;
+  double acc = 0.0;
+#pragma unroll
+  for (int k = 0; k < KM; ++k)
+    if (k * kTailPart < n8) acc += m[k] * r[k * kTailPart + part];
+#pragma unroll
+  for (int w = 1; w < kTailPart; w *= 2) acc += __shfl_xor(acc, w, kWave);
+  __syncthreads();  // every thread has read r
+  if (part == 0 && o < n8) ((TT*)lds)[n + o] = TT(acc);
+  __syncthreads();
+}
+
 // Algorithm 4 on levels lt..1 of one problem; levels >= 2 are stored as T,
 // level 1 as T1.  Thread c owns cell c of every level.  Going down, the
 // restricted residual of a level stays in the registers of the thread that
 // owns the coarse cell (and is kept in the level's right-hand-side buffer for
 // the way up); going up, the coarse correction passes through LDS and each
 // level's stored iterate and right-hand side are fetched one level ahead.
+// Levels P.tml..1 (0: none) are the matrix.
 template <typename T, typename T1>
 __device__ __forceinline__ void tail_run(const ProbD& P, int lt, int K, char* lds) {
   const int c = threadIdx.x;
   constexpr bool kPrefetch = sizeof(T) == 4;  // FP64 lacks the registers
   T R[1][8], G[1][8];
   T1 R1[1][8], G1[1][8];
+  const int lm = P.tml;  // the turn: the matrix, or level 1's sweeps
+  const int low = lm > 0 ? lm : 1;
+  const ElConst<T> k = tail_consts<T>(P);
   // gather tables: tb for the level being swept, tn fetched one level ahead
   // (order of use: lt, ..., 2, 1, 2, ..., lt)
   TailTab tb[1], tn[1];
-  if (kPrefetch) tail_tab_load(P, lt, c, tn);
+  if (kPrefetch && lt > lm) tail_tab_load(P, lt, c, tn);
   if (lt >= 2)
     tail_load1<T>(P.lv[lt], P.lv[lt].r, c, R);
   else
     tail_load1<T1>(P.lv[1], P.lv[1].r, c, R1);
   // ---- descent: K pre-smoothing sweeps from zero, residual, restriction
-  for (int l = lt; l >= 2; --l) {
+  for (int l = lt; l > low; --l) {
     const LevelD& V = P.lv[l];
     const int nx = V.nx, ny = V.ny, n = nx * ny;
     T* sD = (T*)lds;
     T* sG = sD + n;
-    const ElConst<T> k = tail_consts<T>(P);
     if (kPrefetch) {
       tb[0] = tn[0];
-      tail_tab_load(P, l - 1, c, tn);
+      if (l - 1 > lm) tail_tab_load(P, l - 1, c, tn);
     } else {
       tail_tab_load(P, l, c, tb);
     }
-    tail_zero(G);
-    for (int s = 0; s < K; ++s) tail_relax<T, 1>(k, n, tb, G, R, sD, sG, true);
+    tail_first<T>(k, n, tb, G, R, sG);
+    for (int s = 1; s < K; ++s) tail_relax<T, 1>(k, n, tb, G, R, sD, sG, true);
     tail_store1<T>(V, V.gA, c, G);
     tail_relax<T, 1>(k, n, tb, G, R, sD, sG, false);
     __syncthreads();  // every pull has read sG
@@ -1601,8 +1771,8 @@ __device__ __forceinline__ void tail_run(const ProbD& P, int lt, int K, char* ld
     const int cnx = nx / 2, cn = cnx * (ny / 2);
     T sum[8];
     if (c < cn) {
-      const int X = c % cnx, Y = c / cnx;
-      const int f0 = (2 * Y) * nx + 2 * X, f1 = f0 + nx;
+      // fine cell (2 X, 2 Y) of coarse cell (X, Y) = c
+      const int f0 = 2 * c + 2 * cnx * tail_row(c, C.inv_nx), f1 = f0 + nx;
 #pragma unroll
       for (int q = 0; q < 8; ++q) sum[q] = (sG[q * n + f0] + sG[q * n + f0 + 1]) + (sG[q * n + f1] + sG[q * n + f1 + 1]);
     } else {
@@ -1612,35 +1782,35 @@ __device__ __forceinline__ void tail_run(const ProbD& P, int lt, int K, char* ld
     if (l - 1 >= 2) {
 #pragma unroll
       for (int q = 0; q < 8; ++q) R[0][q] = sum[q];
-      tail_store1<T>(C, C.r, c, R);
+      if (l - 1 > lm) tail_store1<T>(C, C.r, c, R);
     } else {
 #pragma unroll
       for (int q = 0; q < 8; ++q) R1[0][q] = T1(sum[q]);
-      tail_store1<T1>(C, C.r, c, R1);
+      if (lm == 0) tail_store1<T1>(C, C.r, c, R1);
     }
     __syncthreads();  // sG is reused by the next level
   }
-  // prefetch level 2's stored iterate and right-hand side for the way up (in
-  // FP64 the registers are not there: those levels load when they start)
+  // prefetch the next level's stored iterate and right-hand side for the way
+  // up (in FP64 the registers are not there: those levels load when they start)
   T Gn[1][8], Rn[1][8];
-  if (kPrefetch && lt >= 2) {
-    tail_load1<T>(P.lv[2], P.lv[2].gA, c, Gn);
-    tail_load1<T>(P.lv[2], P.lv[2].r, c, Rn);
+  if (kPrefetch && lt > low) {
+    tail_load1<T>(P.lv[low + 1], P.lv[low + 1].gA, c, Gn);
+    tail_load1<T>(P.lv[low + 1], P.lv[low + 1].r, c, Rn);
   }
-  // ---- coarsest level: its smoothing sweeps (2K unless set) from zero
-  {
+  if (lm == 0) {
+    // ---- coarsest level: its smoothing sweeps (2K unless set) from zero
     const LevelD& V = P.lv[1];
     const int n = V.nx * V.ny;
     T1* sD = (T1*)lds;
     T1* sG = sD + n;
-    const ElConst<T1> k = tail_consts<T1>(P);
+    const ElConst<T1> k1 = tail_consts<T1>(P);
     if (kPrefetch)
       tb[0] = tn[0];
     else
       tail_tab_load(P, 1, c, tb);
     if (kPrefetch && lt >= 2) tail_tab_load(P, 2, c, tn);
-    tail_zero(G1);
-    for (int s = 0; s < P.csweeps; ++s) tail_relax<T1, 1>(k, n, tb, G1, R1, sD, sG, true);
+    tail_first<T1>(k1, n, tb, G1, R1, sG);
+    for (int s = 1; s < P.csweeps; ++s) tail_relax<T1, 1>(k1, n, tb, G1, R1, sD, sG, true);
     tail_store1<T1>(V, V.gA, c, G1);
     __syncthreads();  // every pull has read sG
     if (c < n) {
@@ -1648,10 +1818,33 @@ __device__ __forceinline__ void tail_run(const ProbD& P, int lt, int K, char* ld
       for (int q = 0; q < 8; ++q) sG[q * n + c] = G1[0][q];
     }
     __syncthreads();
+  } else {
+    if (kPrefetch && lt > lm) tail_tab_load(P, lm + 1, c, tn);
+    if (lm == 1)
+      tail_dense<T1, T1>(P, R1, lds);
+    else
+      tail_dense<T, T>(P, R, lds);
+    if (lt == lm) {  // the matrix is the whole tail
+      const LevelD& V = P.lv[lm];
+      const int n = V.nx * V.ny;
+      if (lm == 1) {
+        if (c < n) {
+#pragma unroll
+          for (int q = 0; q < 8; ++q) G1[0][q] = ((const T1*)lds)[n + q * n + c];
+        }
+        tail_store1<T1>(V, V.gA, c, G1);
+      } else {
+        if (c < n) {
+#pragma unroll
+          for (int q = 0; q < 8; ++q) G[0][q] = ((const T*)lds)[n + q * n + c];
+        }
+        tail_store1<T>(V, V.gA, c, G);
+      }
+    }
   }
   // ---- ascent: iterate plus injected coarse correction, K post-smoothing
   // sweeps; the coarse level's result sits in LDS after its sD plane
-  for (int l = 2; l <= lt; ++l) {
+  for (int l = low + 1; l <= lt; ++l) {
     const LevelD& V = P.lv[l];
     const int nx = V.nx, ny = V.ny, n = nx * ny;
     const int cn = (nx / 2) * (ny / 2);
@@ -1666,7 +1859,7 @@ __device__ __forceinline__ void tail_run(const ProbD& P, int lt, int K, char* ld
       tail_load1<T>(V, V.r, c, R);
     }
     if (c < n) {
-      const int ci = ((c / nx) >> 1) * (nx / 2) + ((c % nx) >> 1);
+      const int y = tail_row(c, V.inv_nx), ci = (y >> 1) * (nx / 2) + ((c - y * nx) >> 1);
       if (l == 2) {
         const T1* ex = (const T1*)lds + cn;
 #pragma unroll
@@ -1684,7 +1877,6 @@ __device__ __forceinline__ void tail_run(const ProbD& P, int lt, int K, char* ld
     __syncthreads();  // the sweeps' sD overlaps the coarse result just read
     T* sD = (T*)lds;
     T* sG = sD + n;
-    const ElConst<T> k = tail_consts<T>(P);
     if (kPrefetch) {
       tb[0] = tn[0];
       if (l + 1 <= lt) tail_tab_load(P, l + 1, c, tn);
@@ -1746,8 +1938,7 @@ __device__ __forceinline__ void tail_restrict(const ProbD& P, int l, const T (&G
   const int cnx = nx / 2, cn = cnx * (ny / 2);
   T sum[8];
   if (c < cn) {
-    const int X = c % cnx, Y = c / cnx;
-    const int f0 = (2 * Y) * nx + 2 * X, f1 = f0 + nx;
+    const int f0 = 2 * c + 2 * cnx * tail_row(c, C.inv_nx), f1 = f0 + nx;  // fine cell (2 X, 2 Y) of (X, Y) = c
 #pragma unroll
     for (int q = 0; q < 8; ++q) sum[q] = (sG[q * n + f0] + sG[q * n + f0 + 1]) + (sG[q * n + f1] + sG[q * n + f1 + 1]);
   } else {
@@ -1829,7 +2020,7 @@ __device__ __forceinline__ void tail_post(const ProbD& P, int l, int K, char* ld
   tail_load1<T>(V, V.gA, c, G);
   tail_load1<T>(V, V.r, c, R);
   if (c < n) {
-    const int ci = ((c / nx) >> 1) * (nx / 2) + ((c % nx) >> 1);
+    const int y = tail_row(c, V.inv_nx), ci = (y >> 1) * (nx / 2) + ((c - y * nx) >> 1);
     const TC* ex = (const TC*)lds + cn;
 #pragma unroll
     for (int q = 0; q < 8; ++q) G[0][q] += T(ex[q * cn + ci]);
@@ -1895,14 +2086,24 @@ __device__ __forceinline__ void tail_run_shaped(const ProbD& P, int lt, int K, i
 // self-force and its wall terms (per cell and population, scaled like the
 // post-collision populations) to the pulled values; R = 0 there.
 
+// the finest level's force of this thread's cell, and its wall terms in LDS
+// (thread c's own entries q kTailThreads + c; read by the waves that hold a
+// wall cell alone)
+template <typename T>
+struct TailFine {
+  T Fx, Fy;
+  const T* add;
+  bool wall;  // uniform over the wave
+};
+
 // one application of S on the finest level held by the workgroup (one cell
-// per thread): as tail_relax with the force (Fx, Fy) and wall terms `add`.
+// per thread): as tail_relax with the force and wall terms f.
 // mode 1: G <- (1 - gamma) G + gamma S(G); 0: G <- G - S(G); 3 (the
 // measuring sweep): G <- (1 - gamma) G + gamma S(G) from the unscaled S(G),
 // adding ||G - S(G)||^2 and ||G||^2 of the cell to (mr, mg) in FP64
 template <typename T>
 __device__ __forceinline__ void tail_relax_fine(const ElConst<T>& k, int n, const TailTab (&tb)[1], T (&G)[1][8],
-                                                T Fx, T Fy, const T (&add)[8], T* sD, T* sG, int mode,
+                                                const TailFine<T>& f, T* sD, T* sG, int mode,
                                                 double* mr = nullptr, double* mg = nullptr) {
   const int c = threadIdx.x;
   const bool blend = mode == 1;
@@ -1925,7 +2126,7 @@ __device__ __forceinline__ void tail_relax_fine(const ElConst<T>& k, int n, cons
     T u[8], s8[8];
 #pragma unroll
     for (int q = 0; q < 8; ++q) u[q] = G[0][q];
-    el_collide(u, k.cstar * gx_ + Fx, k.cstar * gy_ + Fy, k, s8, sc);
+    el_collide(u, k.cstar * gx_ + f.Fx, k.cstar * gy_ + f.Fy, k, s8, sc);
 #pragma unroll
     for (int q = 0; q < 8; ++q) sG[q * n + c] = s8[q];
   }
@@ -1936,7 +2137,8 @@ __device__ __forceinline__ void tail_relax_fine(const ElConst<T>& k, int n, cons
     for (int q = 0; q < 8; ++q) {
       const uint32_t code = (q & 1) ? hi16(tb[0].pl[q >> 1]) : lo16(tb[0].pl[q >> 1]);
       const T v = sG[code & 0x7fffu];
-      const T gi = ((code & 0x8000u) ? -v : v) + sc * add[q];
+      T gi = (code & 0x8000u) ? -v : v;
+      if (f.wall) gi += sc * f.add[q * kTailThreads + c];
       if (mode == 3) {
         const double rho = double(G[0][q]) - double(gi);
         *mr += rho * rho;
@@ -1949,26 +2151,41 @@ __device__ __forceinline__ void tail_relax_fine(const ElConst<T>& k, int n, cons
   }
 }
 
-// the finest level's force and wall terms of this thread's cell
+// the finest level's force and wall terms, loaded into LDS once per launch
+// (every phase of every cycle uses them; registers held across the phases
+// would spill): 8 planes of wall terms, then the force's two.  A serial chain
+// of sweeps bounds the launch; the Terzaghi column 8 x 128 in FP64, 50 cycles:
+// 2.22 ms per step with global loads in each phase, 2.07 so
 template <typename T>
-__device__ __forceinline__ void tail_fine_terms(const ProbD& P, const LevelD& V, int c, T& Fx, T& Fy, T (&add)[8]) {
-  Fx = Fy = T(0);
+__device__ __forceinline__ bool tail_fine_load(const ProbD& P, const LevelD& V, T* sF) {
+  const int c = threadIdx.x;
+  bool wall = false;
+  if (c < V.nx * V.ny) {
+    const int64_t idx = (int64_t)tail_row(c, V.inv_nx) * (V.pitch - V.nx) + c;
+    const T* F = (const T*)P.Ft;
+    const T* ad = (const T*)P.addt;
 #pragma unroll
-  for (int q = 0; q < 8; ++q) add[q] = T(0);
-  if (c >= V.nx * V.ny) return;
-  const int64_t idx = (int64_t)(c / V.nx) * V.pitch + c % V.nx;
-  const T* F = (const T*)P.Ft;
-  const T* ad = (const T*)P.addt;
-  Fx = F[idx];
-  Fy = F[V.plane + idx];
-#pragma unroll
-  for (int q = 0; q < 8; ++q) add[q] = ad[q * V.plane + idx];
+    for (int q = 0; q < 8; ++q) {
+      const T v = ad[q * V.plane + idx];
+      wall = wall || v != T(0);
+      sF[q * kTailThreads + c] = v;
+    }
+    sF[8 * kTailThreads + c] = F[idx];
+    sF[9 * kTailThreads + c] = F[V.plane + idx];
+  }
+  return __any(wall);
+}
+template <typename T>
+__device__ __forceinline__ TailFine<T> tail_fine_terms(const T* sF, bool wall) {
+  const int c = threadIdx.x;
+  return {sF[8 * kTailThreads + c], sF[9 * kTailThreads + c], sF, wall};
 }
 
 // pre-smoothing of the finest level L from buffer A or B (npre sweeps), the
 // iterate stored to A, the residual restricted into level L - 1's r
 template <typename T, typename T1>
-__device__ __forceinline__ void tail_fine_pre_g(const ProbD& P, int L, int npre, T (&G)[1][8], char* lds) {
+__device__ __forceinline__ void tail_fine_pre_g(const ProbD& P, int L, int npre, T (&G)[1][8], char* lds, const T* sF,
+                                                bool wall) {
   const int c = threadIdx.x;
   const LevelD& V = P.lv[L];
   const int nx = V.nx, ny = V.ny, n = nx * ny;
@@ -1976,38 +2193,28 @@ __device__ __forceinline__ void tail_fine_pre_g(const ProbD& P, int L, int npre,
   T* sG = sD + n;
   const ElConst<T> k = tail_consts<T>(P);
   TailTab tb[1];
-  T add[8], Fx, Fy;
   tail_tab_load(P, L, c, tb);
-  tail_fine_terms<T>(P, V, c, Fx, Fy, add);
-  for (int s = 0; s < npre; ++s) tail_relax_fine<T>(k, n, tb, G, Fx, Fy, add, sD, sG, 1);
+  const TailFine<T> f = tail_fine_terms<T>(sF, wall);
+  for (int s = 0; s < npre; ++s) tail_relax_fine<T>(k, n, tb, G, f, sD, sG, 1);
   tail_store1<T>(V, V.gA, c, G);
-  tail_relax_fine<T>(k, n, tb, G, Fx, Fy, add, sD, sG, 0);
+  tail_relax_fine<T>(k, n, tb, G, f, sD, sG, 0);
   tail_restrict<T, T1>(P, L, G, lds);
-}
-
-template <typename T, typename T1>
-__device__ __forceinline__ void tail_fine_pre(const ProbD& P, int L, int npre, bool from_b, char* lds) {
-  const LevelD& V = P.lv[L];
-  T G[1][8];
-  tail_load1<T>(V, from_b ? V.gB : V.gA, threadIdx.x, G);
-  tail_fine_pre_g<T, T1>(P, L, npre, G, lds);
 }
 
 // post-smoothing of the finest level: its stored iterate plus the injected
 // coarse correction (in LDS, type TC), K sweeps, stored to A
 template <typename T, typename TC>
-__device__ __forceinline__ void tail_fine_post(const ProbD& P, int L, int K, char* lds) {
+__device__ __forceinline__ void tail_fine_post(const ProbD& P, int L, int K, char* lds, const T* sF, bool wall) {
   const int c = threadIdx.x;
   const LevelD& V = P.lv[L];
   const int nx = V.nx, ny = V.ny, n = nx * ny;
   const int cn = (nx / 2) * (ny / 2);
   TailTab tb[1];
-  T G[1][8], add[8], Fx, Fy;
+  T G[1][8];
   tail_tab_load(P, L, c, tb);
   tail_load1<T>(V, V.gA, c, G);
-  tail_fine_terms<T>(P, V, c, Fx, Fy, add);
   if (c < n) {
-    const int ci = ((c / nx) >> 1) * (nx / 2) + ((c % nx) >> 1);
+    const int y = tail_row(c, V.inv_nx), ci = (y >> 1) * (nx / 2) + ((c - y * nx) >> 1);
     const TC* ex = (const TC*)lds + cn;
 #pragma unroll
     for (int q = 0; q < 8; ++q) G[0][q] += T(ex[q * cn + ci]);
@@ -2016,7 +2223,8 @@ __device__ __forceinline__ void tail_fine_post(const ProbD& P, int L, int K, cha
   T* sD = (T*)lds;
   T* sG = sD + n;
   const ElConst<T> k = tail_consts<T>(P);
-  for (int s = 0; s < K; ++s) tail_relax_fine<T>(k, n, tb, G, Fx, Fy, add, sD, sG, 1);
+  const TailFine<T> f = tail_fine_terms<T>(sF, wall);
+  for (int s = 0; s < K; ++s) tail_relax_fine<T>(k, n, tb, G, f, sD, sG, 1);
   tail_store1<T>(V, V.gA, c, G);
 }
 
@@ -2026,23 +2234,26 @@ struct TailFullState {
   double ratio, rr, gg;
   int stopped, count;
 };
-constexpr int kTailFullLdsBytes = kTailLdsBytes + 64;
+// (levels, the test's state, the finest level's terms: 156 of 160 KiB in FP64)
+template <typename T> constexpr int tail_full_lds() { return kTailLdsBytes + 64 + 10 * kTailThreads * (int)sizeof(T); }
+static_assert(tail_full_lds<double>() <= 160 * 1024, "one workgroup's LDS");
 static_assert(sizeof(TailFullState) <= 64, "state fits its LDS slot");
 
 // one cycle of the whole problem: pre-smoothing from buffer A or B, the
 // coarse correction (one visit, or two for W (W, W) and F (F, V)), the
 // post-smoothing into A
 template <typename T>
-__device__ __forceinline__ void tail_full_cycle(const ProbD& P, const TailL& a, int npre, T (&G)[1][8], char* lds) {
+__device__ __forceinline__ void tail_full_cycle(const ProbD& P, const TailL& a, int npre, T (&G)[1][8], char* lds,
+                                                const T* sF, bool wall) {
   const int L = P.L;
-  tail_fine_pre_g<T, double>(P, L, npre, G, lds);
+  tail_fine_pre_g<T, double>(P, L, npre, G, lds, sF, wall);
   const int visits = a.shape != 0 ? 2 : 1;
   for (int v = 0; v < visits; ++v)  // one call site: one inlined copy of the recursion
     tail_run_shaped<T, double>(P, L - 1, a.K, v == 0 ? a.shape : (a.shape == 1 ? 1 : 0), v == 0, lds);
   if (L == 2)
-    tail_fine_post<T, double>(P, L, a.K, lds);
+    tail_fine_post<T, double>(P, L, a.K, lds, sF, wall);
   else
-    tail_fine_post<T, T>(P, L, a.K, lds);
+    tail_fine_post<T, T>(P, L, a.K, lds, sF, wall);
 }
 
 // the measuring sweep of the adaptive schedule on the finest level: one
@@ -2050,7 +2261,8 @@ __device__ __forceinline__ void tail_full_cycle(const ProbD& P, const TailL& a, 
 // cycle continues from, left in G), with the FP64 squares ||g - S(g)||^2 and
 // ||g||^2 summed over the level in a fixed order (lanes, then waves)
 template <typename T>
-__device__ __forceinline__ void tail_measure(const ProbD& P, char* lds, T (&G)[1][8], double& rr, double& gg) {
+__device__ __forceinline__ void tail_measure(const ProbD& P, char* lds, T (&G)[1][8], double& rr, double& gg, const T* sF,
+                                             bool wall) {
   const int c = threadIdx.x;
   const LevelD& V = P.lv[P.L];
   const int n = V.nx * V.ny;
@@ -2058,12 +2270,10 @@ __device__ __forceinline__ void tail_measure(const ProbD& P, char* lds, T (&G)[1
   T* sG = sD + n;
   const ElConst<T> k = tail_consts<T>(P);
   TailTab tb[1];
-  T add[8], Fx, Fy;
   tail_tab_load(P, P.L, c, tb);
   tail_load1<T>(V, V.gA, c, G);
-  tail_fine_terms<T>(P, V, c, Fx, Fy, add);
   double r = 0.0, g = 0.0;
-  tail_relax_fine<T>(k, n, tb, G, Fx, Fy, add, sD, sG, 3, &r, &g);
+  tail_relax_fine<T>(k, n, tb, G, tail_fine_terms<T>(sF, wall), sD, sG, 3, &r, &g);
 #pragma unroll
   for (int o = kWave / 2; o > 0; o >>= 1) {
     r += __shfl_down(r, o, kWave);
@@ -2109,14 +2319,16 @@ __global__ __launch_bounds__(kTailThreads) void k_tail_full(TailL a) {
     st->rr = 0.0;
     st->gg = 0.0;
   }
+  T* sF = (T*)(lds + kTailLdsBytes + 64);
+  const bool wall = tail_fine_load<T>(P, P.lv[L], sF);
   T G[1][8];
   tail_load1<T>(P.lv[L], (!a.loop && a.fine_in) ? P.lv[L].gB : P.lv[L].gA, threadIdx.x, G);
   int npre = a.loop ? a.K : a.fine_pre;
   for (int pass = 0; pass <= a.ne_max; ++pass) {
-    tail_full_cycle<T>(P, a, npre, G, lds);
+    tail_full_cycle<T>(P, a, npre, G, lds, sF, wall);
     if (!a.loop) break;
     double rr, gg;
-    tail_measure<T>(P, lds, G, rr, gg);
+    tail_measure<T>(P, lds, G, rr, gg, sF, wall);
     if (threadIdx.x == 0) {
       st->rr = rr;
       st->gg = gg;
@@ -2176,7 +2388,7 @@ hipError_t launch_tail(const TailL& a, int nprobs, bool dbl, hipStream_t s) {
                          (const void*)k_tail_full<float>,   (const void*)k_tail_full<double>};
     for (int i = 0; i < 6; ++i) {
       const hipError_t e = hipFuncSetAttribute(ks[i], hipFuncAttributeMaxDynamicSharedMemorySize,
-                                               i >= 4 ? kTailFullLdsBytes : kTailLdsBytes);
+                                               i == 4 ? tail_full_lds<float>() : (i == 5 ? tail_full_lds<double>() : kTailLdsBytes));
       if (e != hipSuccess) return e;
     }
     attr = true;
@@ -2185,9 +2397,9 @@ hipError_t launch_tail(const TailL& a, int nprobs, bool dbl, hipStream_t s) {
   // prefetching kernel; other shapes and continued visits the shaped one
   const bool shaped = a.shape != 0 || !a.from_zero;
   if (a.full && dbl)
-    hipLaunchKernelGGL(k_tail_full<double>, dim3(nprobs), dim3(kTailThreads), kTailFullLdsBytes, s, a);
+    hipLaunchKernelGGL(k_tail_full<double>, dim3(nprobs), dim3(kTailThreads), tail_full_lds<double>(), s, a);
   else if (a.full)
-    hipLaunchKernelGGL(k_tail_full<float>, dim3(nprobs), dim3(kTailThreads), kTailFullLdsBytes, s, a);
+    hipLaunchKernelGGL(k_tail_full<float>, dim3(nprobs), dim3(kTailThreads), tail_full_lds<float>(), s, a);
   else if (shaped && dbl)
     hipLaunchKernelGGL(k_tail_shaped<double>, dim3(nprobs), dim3(kTailThreads), kTailLdsBytes, s, a);
   else if (shaped)

@@ -63,3 +63,38 @@ def test_wall_types_in_multi_application_launches(lbm, walls, nx, ny):
             assert max(e.values()) <= tol  # no data on periodic and symmetry sides: the fields stay zero there
             if prec == "fp64":
                 assert float(np.abs(A["eta"] - B["eta"]).max()) <= tol * float(np.abs(B["eta"]).max())
+
+
+@pytest.mark.parametrize("shape", [(4, 4, 1), (4, 4, 2), (8, 8, 2), (8, 8, 3), (16, 16, 4), (8, 2, 1), (12, 12, 3),
+                                   (20, 20, 3), (40, 24, 4)])
+@pytest.mark.parametrize("walls", ["SSST", "PPDT", "DTSD"])
+@pytest.mark.parametrize("sweeps", [0, 6])
+def test_smallest_levels_as_a_matrix(lbm, shape, walls, sweeps):
+    """The V-cycle's levels of at most 16 cells run as one matrix: the coarse
+    cycle from zero on the coarse tail's top level (which the matrix covers
+    whole, in part or not at all here) and time steps against the oracle."""
+    nx, ny, L = shape
+    if walls[0] != "P" and nx >> (L - 1) < 2:
+        pytest.skip("fewer than two cells across on the coarsest level")
+    p = _problem(walls, 2 * nx, 2 * ny).replace(levels=L + 1, coarse_sweeps=sweeps)
+    o = Oracle(p, threads=oracle_threads())
+    rng = np.random.default_rng(5)
+    s = lbm.Solver(p, "fp64")
+    lnx, lny = s.level_shape(L)
+    r = rng.standard_normal((8, lny, lnx)) * 1e-3
+    z = np.zeros_like(r)
+    e = rel(s.mg_cycle(L, z, r=r), o.mg_cycle(L, z, r=r))
+    s.close()
+    o = Oracle(p, threads=oracle_threads())
+    o.step(3)
+    B = o.fields()
+    errs = []
+    for prec, tol in (("fp64", 1e-10), ("fp32_shifted", 1e-5)):
+        s = lbm.Solver(p, prec)
+        s.step(3)
+        A = s.fields()
+        s.close()
+        errs.append((max(rel(A[k], B[k]) for k in ("eta", "p")), tol))
+    print(shape, walls, sweeps, e, errs, flush=True)
+    assert e < 1e-11
+    assert all(v < tol for v, tol in errs)
