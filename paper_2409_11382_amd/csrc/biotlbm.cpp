@@ -13,10 +13,12 @@
 #include <cstdlib>
 #include <cstring>
 #include <deque>
+#include <exception>
 #include <map>
 #include <memory>
 #include <mutex>
 #include <string>
+#include <thread>
 #include <vector>
 
 #include "../../include/biotlbm.h"
@@ -444,11 +446,16 @@ bp_status down(hipStream_t st, bool dbl, const void* srcd, int nx, int ny, int p
              : download_planes<float>(st, srcd, nx, ny, pitch, plane, dst, m);
 }
 
+void set_loads_of(Prob& P, bool body, bool src) {
+  P.has_body = body;
+  P.has_src = src;
+  P.d.fbody = body ? (const double*)(P.base + P.lo.off_fbody) : nullptr;
+  P.d.src = src ? (const double*)(P.base + P.lo.off_src) : nullptr;
+}
+
 bp_status upload_loads(hipStream_t st, Prob& P, const double* body_f, const double* source_s) {
   const int nx = P.nx, ny = P.ny;
   const size_t N = (size_t)nx * ny;
-  P.has_body = body_f != nullptr;
-  P.has_src = source_s != nullptr;
   std::vector<double> b(2 * N), sv(N);
   if (body_f)
     for (size_t k = 0; k < 2 * N; ++k) b[k] = P.h * P.h * P.c0 * body_f[k];
@@ -456,8 +463,7 @@ bp_status upload_loads(hipStream_t st, Prob& P, const double* body_f, const doub
     for (size_t k = 0; k < N; ++k) sv[k] = P.dt * source_s[k];
   BPCHK(upload_planes<double>(st, P.base + P.lo.off_fbody, nx, ny, P.lo.pitch, P.lo.plane, body_f ? b.data() : nullptr, 2));
   BPCHK(upload_planes<double>(st, P.base + P.lo.off_src, nx, ny, P.lo.pitch, P.lo.plane, source_s ? sv.data() : nullptr, 1));
-  P.d.fbody = P.has_body ? (const double*)(P.base + P.lo.off_fbody) : nullptr;
-  P.d.src = P.has_src ? (const double*)(P.base + P.lo.off_src) : nullptr;
+  set_loads_of(P, body_f != nullptr, source_s != nullptr);
   return BP_OK;
 }
 
@@ -638,7 +644,7 @@ bp_status setup_problem(const bp_problem* p, const Layout& lo, char* base, hipSt
 }
 
 // ---------------------------------------------------------------- engine
-enum OpKind { OP_SWEEP, OP_TAIL, OP_FORCE, OP_REBASE_EL, OP_REBASE_FORCE, OP_AD_RESET, OP_FLOW, OP_FINALIZE, OP_ADVANCE, OP_INIT, OP_EXTRACT };
+enum OpKind { OP_SWEEP, OP_TAIL, OP_FORCE, OP_REBASE_EL, OP_REBASE_FORCE, OP_AD_RESET, OP_FLOW, OP_FINALIZE, OP_ADVANCE, OP_INIT };
 
 struct Op {
   OpKind kind;
@@ -704,6 +710,25 @@ struct DepthLists {
   int tail_off = 0, tail_cnt = 0;  // problems whose coarse tail starts here
 };
 
+// pinned host memory in slots, through which fields leave and loads enter the
+// device: the fields kernel writes a slot directly and threads copy the slots
+// to the caller's arrays, whose page faults bound a large readout.  Fields by
+// pageable copies of whole planes -> by slots: 64^2 0.16 -> 0.03 ms, 512^2
+// 1.25 -> 0.50, 2048^2 (201 MB) 31 -> 9.5, the 48 of a batch 50 -> 16.
+// Slots of 512 KiB: writing one takes longer than launching its kernel.
+struct Stage {
+  static constexpr size_t kSlot = 512 << 10;
+  static constexpr int kSlots = 8;
+  char* mem = nullptr;
+  size_t slot = 0;  // bytes of a slot, before it a header of kHead bytes
+  int n = 0;        // slots (0: none, the caller copies)
+  hipEvent_t ev[kSlots] = {};
+  bool busy[kSlots] = {};  // an upload reads the slot until ev
+  static constexpr size_t kHead = 64;
+  int* head(int i) const { return (int*)(mem + i * (slot + kHead)); }
+  char* data(int i) const { return mem + i * (slot + kHead) + kHead; }
+};
+
 struct Engine {
   hipStream_t stream = nullptr;
   bool fdbl = true, shift = false;
@@ -755,6 +780,7 @@ struct Engine {
   double* host_pin = nullptr;
   bool own_pin = false;        // host_pin from hipHostMalloc (else host_buf)
   double host_buf[4] = {};     // staging of engines that allocate nothing
+  Stage stage;
 };
 
 int tgroup(const Engine& E, const Prob& P, int depth) {
@@ -1200,9 +1226,6 @@ hipError_t run_op(const Engine& E, const Op& o) {
     case OP_FLOW:
       if (E.fdbl) return E.shift ? launch_tflow<double, true>(o.cl, o.count, s) : launch_tflow<double, false>(o.cl, o.count, s);
       return E.shift ? launch_tflow<float, true>(o.cl, o.count, s) : launch_tflow<float, false>(o.cl, o.count, s);
-    case OP_EXTRACT:
-      if (E.fdbl) return E.shift ? launch_extract<double, true>(o.cl, o.count, s) : launch_extract<double, false>(o.cl, o.count, s);
-      return E.shift ? launch_extract<float, true>(o.cl, o.count, s) : launch_extract<float, false>(o.cl, o.count, s);
     case OP_TAIL: return launch_tail(o.tl, o.count, E.fdbl, s);
     case OP_FINALIZE: return launch_finalize(o.pl, o.count, s);
     case OP_AD_RESET: return launch_ad_reset(o.pl, s);
@@ -1291,9 +1314,6 @@ bp_status build_graph(Engine& E) {
       BPCHK(upload_tile_counts(E, offsetof(ProbD, ntiles_fine2), o.apps, o.alt));
   if (E.use_graph && E.stream) {
     BPCHK(capture_ops(E, E.step_ops, &E.graph));
-    std::vector<Op> four;
-    for (int k = 0; k < 4; ++k) four.insert(four.end(), E.step_ops.begin(), E.step_ops.end());
-    BPCHK(capture_ops(E, four, &E.graph4));
   }
   E.graph_valid = true;
   return BP_OK;
@@ -1341,8 +1361,45 @@ bp_status engine_init(Engine& E, char* area, size_t area_bytes, size_t probs_cap
   return BP_OK;
 }
 
+// a stream under capture refuses what reads or writes host memory: it takes
+// the general copies, which report that
+bool staged(const Engine& E, size_t row_bytes) {
+  hipStreamCaptureStatus c = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(E.stream, &c) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return E.stage.n > 0 && row_bytes <= E.stage.slot && c == hipStreamCaptureStatusNone;
+}
+
+// bytes of a problem's fields
+size_t field_bytes(const bp_problem& p) { return (size_t)p.nx * p.ny * 6 * sizeof(double); }
+
+// staging for fields of up to `bytes`; without it (no memory) fields and loads
+// go through pageable copies
+void stage_init(Stage& S, size_t bytes) {
+  S.slot = std::min(Stage::kSlot, align_up(bytes));
+  const int n = (int)std::min<size_t>(Stage::kSlots, (bytes + S.slot - 1) / S.slot);
+  if (hipHostMalloc((void**)&S.mem, n * (S.slot + Stage::kHead), hipHostMallocDefault) != hipSuccess) {
+    (void)hipGetLastError();
+    S.mem = nullptr;
+    return;
+  }
+  for (; S.n < n; ++S.n)
+    if (hipEventCreateWithFlags(&S.ev[S.n], hipEventDisableTiming) != hipSuccess) {
+      (void)hipGetLastError();
+      break;
+    }
+}
+void stage_release(Stage& S) {
+  for (int i = 0; i < S.n; ++i) (void)hipEventDestroy(S.ev[i]);
+  if (S.mem) (void)hipHostFree(S.mem);
+  S = Stage();
+}
+
 void engine_release(Engine& E) {
-  (void)hipStreamSynchronize(E.stream);  // queued work may still read the pinned staging buffer
+  (void)hipStreamSynchronize(E.stream);  // queued work may still read the pinned staging buffers
+  stage_release(E.stage);
   if (E.graph) (void)hipGraphExecDestroy(E.graph);
   E.graph = nullptr;
   if (E.graph4) (void)hipGraphExecDestroy(E.graph4);
@@ -1366,6 +1423,11 @@ bp_status fixed_step(Engine& E, int* left = nullptr) {
   TraceRange r("coupled step");
   if (!E.graph_valid) BPCHK(build_graph(E));
   int n = 1;
+  if (left && *left >= 4 && E.graph && !E.graph4) {  // batches and servers take one step at a time
+    std::vector<Op> four;
+    for (int k = 0; k < 4; ++k) four.insert(four.end(), E.step_ops.begin(), E.step_ops.end());
+    BPCHK(capture_ops(E, four, &E.graph4));
+  }
   if (left && *left >= 4 && E.graph4) {
     HIPCHK(hipGraphLaunch(E.graph4, E.stream));
     n = 4;
@@ -1738,30 +1800,136 @@ bp_status autotune(Engine& E, int steps, bp_tuning* out) {
   return BP_OK;
 }
 
-bp_status extract_fields(Engine& E) {
-  std::vector<Op> ops{cell_op(E, OP_EXTRACT)};
-  return run_ops(E, ops);
+hipError_t extract_rows(const Engine& E, const ExtractL& a, int nx) {
+  if (E.fdbl)
+    return E.shift ? launch_extract<double, true>(a, nx, E.stream) : launch_extract<double, false>(a, nx, E.stream);
+  return E.shift ? launch_extract<float, true>(a, nx, E.stream) : launch_extract<float, false>(a, nx, E.stream);
+}
+
+// fields through the staging slots: each thread takes chunks of rows with a
+// slot of its own; flags as in ExtractL
+bp_status staged_fields(Engine& E, Prob& P, const ExtractL& all, double* eta, double* p, double* sigma, int flags[2]) {
+  Stage& S = E.stage;
+  const int nx = P.nx, ny = P.ny;
+  const size_t N = (size_t)nx * ny;
+  int rows = (int)std::min<size_t>(S.slot / ((size_t)nx * 6 * sizeof(double)), ny);
+  if (rows > kCellBY && rows < ny) rows -= rows % kCellBY;
+  const int chunks = (ny + rows - 1) / rows, nt = std::min(S.n, chunks);
+  int dev = 0;
+  HIPCHK(hipGetDevice(&dev));
+  struct Result {
+    hipError_t err = hipSuccess;
+    int flags[2] = {0, 0};
+  } res[Stage::kSlots];
+  for (int t = 0; t < nt; ++t)
+    if (S.busy[t]) {
+      HIPCHK(hipEventSynchronize(S.ev[t]));
+      S.busy[t] = false;
+    }
+  auto run = [&](int t, bool own_device) {
+    Result& r = res[t];
+    if (own_device) r.err = hipSetDevice(dev);
+    for (int c = t; c < chunks && r.err == hipSuccess; c += nt) {
+      ExtractL a = all;
+      a.row0 = c * rows;
+      a.rows = std::min(rows, ny - a.row0);
+      const size_t n = (size_t)a.rows * nx, o = (size_t)a.row0 * nx;
+      double* d = (double*)S.data(t);
+      a.eta = d;
+      a.p = d + 2 * n;
+      a.sig = d + 3 * n;
+      a.stride = (int64_t)n;
+      a.flags = S.head(t);
+      a.flags[0] = a.flags[1] = 0;
+      r.err = extract_rows(E, a, nx);
+      if (r.err == hipSuccess) r.err = hipEventRecord(S.ev[t], E.stream);
+      if (r.err == hipSuccess) r.err = hipEventSynchronize(S.ev[t]);
+      if (r.err != hipSuccess) break;
+      for (int k = 0; k < 2; ++k) r.flags[k] |= a.flags[k];
+      for (int k = 0; k < 6; ++k) {
+        double* dst = k < 2 ? eta : (k == 2 ? p : sigma);
+        if (dst) std::memcpy(dst + (k < 2 ? k : (k == 2 ? 0 : k - 3)) * N + o, d + k * n, n * sizeof(double));
+      }
+    }
+  };
+  std::thread th[Stage::kSlots];
+  int started = 1;
+  try {
+    for (; started < nt; ++started) th[started] = std::thread(run, started, true);
+  } catch (const std::exception&) {  // no more threads: their chunks run here
+  }
+  run(0, false);
+  for (int t = started; t < nt; ++t) run(t, false);
+  for (int t = 1; t < started; ++t) th[t].join();
+  for (int t = 0; t < nt; ++t) {
+    HIPCHK(res[t].err);
+    for (int k = 0; k < 2; ++k) flags[k] |= res[t].flags[k];
+  }
+  return BP_OK;
 }
 
 bp_status fields_of(Engine& E, Prob& P, double* eta, double* p, double* sigma, int32_t* step) {
   const size_t N = (size_t)P.nx * P.ny;
-  int flag = 0;
-  HIPCHK(hipMemcpyAsync(&flag, P.d.flags, sizeof(int), hipMemcpyDeviceToHost, E.stream));
-  if (eta) HIPCHK(hipMemcpyAsync(eta, P.d.eta, 2 * N * 8, hipMemcpyDeviceToHost, E.stream));
-  if (sigma) HIPCHK(hipMemcpyAsync(sigma, P.d.sig, 3 * N * 8, hipMemcpyDeviceToHost, E.stream));
-  HIPCHK(hipStreamSynchronize(E.stream));
-  if (p) {
-    BPCHK(download_planes<double>(E.stream, P.d.pout, P.nx, P.ny, P.lo.pitch, P.lo.plane, p, 1));
-    for (size_t k = 0; k < N; ++k) p[k] /= P.c0;
+  const auto it = std::find(E.probs.begin(), E.probs.end(), &P);
+  if (it == E.probs.end()) return fail(BP_ERR_STATE, "the problem is not one of the engine's");
+  ExtractL a{};
+  a.prob = E.d_probs + (it - E.probs.begin());
+  a.c0 = P.c0;
+  int flags[2] = {0, 0};
+  if (staged(E, (size_t)P.nx * 6 * sizeof(double))) {
+    BPCHK(staged_fields(E, P, a, eta, p, sigma, flags));
+  } else {
+    a.eta = P.d.eta;
+    a.sig = P.d.sig;
+    a.stride = (int64_t)N;
+    a.rows = P.ny;
+    HIPCHK(extract_rows(E, a, P.nx));
+    HIPCHK(hipMemcpyAsync(&flags[1], P.d.flags, sizeof(int), hipMemcpyDeviceToHost, E.stream));
+    if (eta) HIPCHK(hipMemcpyAsync(eta, P.d.eta, 2 * N * 8, hipMemcpyDeviceToHost, E.stream));
+    if (sigma) HIPCHK(hipMemcpyAsync(sigma, P.d.sig, 3 * N * 8, hipMemcpyDeviceToHost, E.stream));
+    HIPCHK(hipStreamSynchronize(E.stream));
+    if (p) {
+      BPCHK(download_planes<double>(E.stream, P.d.pout, P.nx, P.ny, P.lo.pitch, P.lo.plane, p, 1));
+      for (size_t k = 0; k < N; ++k) p[k] /= P.c0;
+    }
+    if (eta)
+      for (size_t k = 0; k < 2 * N && !flags[0]; ++k) flags[0] = !std::isfinite(eta[k]);
   }
   if (step) *step = P.step;
-  bool finite = true;
-  if (eta)
-    for (size_t k = 0; k < 2 * N && finite; ++k) finite = std::isfinite(eta[k]);
-  if (flag || !finite) {
+  if (flags[1] || (eta && flags[0])) {
     P.status = BP_ERR_DIVERGED;
     return fail(BP_ERR_DIVERGED, "the solution is not finite");
   }
+  return BP_OK;
+}
+
+// loads through the staging slots, in stream order: the caller's arrays are
+// read before this returns, the device reads the slots when it gets there
+bp_status staged_loads(Engine& E, Prob& P, const double* body_f, const double* source_s) {
+  Stage& S = E.stage;
+  const int nx = P.nx, ny = P.ny, pitch = P.lo.pitch;
+  const int rows = (int)std::min<size_t>(S.slot / ((size_t)pitch * sizeof(double)), ny);
+  int t = 0;
+  for (int c = 0; c < 3; ++c) {
+    const double* src = c < 2 ? (body_f ? body_f + (size_t)c * nx * ny : nullptr) : source_s;
+    const double fac = c < 2 ? P.h * P.h * P.c0 : P.dt;
+    char* dst = P.base + (c < 2 ? P.lo.off_fbody + (size_t)c * P.lo.plane * sizeof(double) : P.lo.off_src);
+    for (int y0 = 0; y0 < ny; y0 += rows, t = (t + 1) % S.n) {
+      const int n = std::min(rows, ny - y0);
+      if (S.busy[t]) HIPCHK(hipEventSynchronize(S.ev[t]));
+      S.busy[t] = false;
+      double* d = (double*)S.data(t);
+      for (int y = 0; y < n; ++y, d += pitch) {
+        for (int x = 0; x < nx; ++x) d[x] = src ? fac * src[(size_t)(y0 + y) * nx + x] : 0.0;
+        for (int x = nx; x < pitch; ++x) d[x] = 0.0;
+      }
+      HIPCHK(launch_copy(dst + (size_t)y0 * pitch * sizeof(double), S.data(t), (size_t)n * pitch * sizeof(double),
+                         E.stream));
+      HIPCHK(hipEventRecord(S.ev[t], E.stream));
+      S.busy[t] = true;
+    }
+  }
+  set_loads_of(P, body_f != nullptr, source_s != nullptr);
   return BP_OK;
 }
 
@@ -1886,7 +2054,6 @@ std::string op_name(const Op& o) {
     case OP_ADVANCE: return "advance";
     case OP_AD_RESET: return "adaptive reset";
     case OP_INIT: return "initial conditions";
-    case OP_EXTRACT: return "extract";
   }
   return "other";
 }
@@ -2177,6 +2344,7 @@ bp_status create_solver(const bp_problem* p, const Layout& lo, char* w, void* hi
   s->ws = w;
   bp_status rc = engine_init(s->E, w + lo.total, need - lo.total, 1, te, st, lo.fdbl, lo.shift, p->K, p->ne_fixed,
                              p->cycle, no_alloc);
+  if (rc == BP_OK && !no_alloc) stage_init(s->E.stage, field_bytes(*p));
   s->E.csweeps = p->coarse_sweeps;
   s->E.lag = p->lag != 0;
   if (s->E.lag) s->E.want_fuse = false;  // the lag runs single applications
@@ -2269,9 +2437,13 @@ bp_status bp_step(bp_solver* s, int32_t nsteps) {
 
 bp_status bp_set_loads(bp_solver* s, const double* body_f, const double* source_s, int32_t reinit) {
   if (!s) return fail(BP_ERR_ARG, "null solver");
-  HIPCHK(hipStreamSynchronize(s->E.stream));
   const bool hb = s->P.has_body, hs = s->P.has_src;
-  BPCHK(upload_loads(s->E.stream, s->P, body_f, source_s));
+  if (staged(s->E, (size_t)s->P.lo.pitch * sizeof(double))) {
+    BPCHK(staged_loads(s->E, s->P, body_f, source_s));
+  } else {
+    HIPCHK(hipStreamSynchronize(s->E.stream));
+    BPCHK(upload_loads(s->E.stream, s->P, body_f, source_s));
+  }
   if (hb != s->P.has_body || hs != s->P.has_src) BPCHK(engine_upload(s->E));
   if (reinit) BPCHK(init_states(s->E));
   return BP_OK;
@@ -2279,7 +2451,6 @@ bp_status bp_set_loads(bp_solver* s, const double* body_f, const double* source_
 
 bp_status bp_get_fields(bp_solver* s, double* eta, double* p, double* sigma, int32_t* step) {
   if (!s) return fail(BP_ERR_ARG, "null solver");
-  BPCHK(extract_fields(s->E));
   return fields_of(s->E, s->P, eta, p, sigma, step);
 }
 
@@ -2663,6 +2834,9 @@ bp_status bp_batch_create(const bp_problem* probs, int32_t n, void* device_ws, s
   for (int i = 0; i < n; ++i) off += los[i].total;
   bp_status rc = engine_init(b->E, w + off, need - off, (size_t)n, te, st, los[0].fdbl, los[0].shift, probs[0].K,
                              probs[0].ne_fixed, probs[0].cycle);
+  size_t most = 0;
+  for (int i = 0; i < n; ++i) most = std::max(most, field_bytes(probs[i]));
+  if (rc == BP_OK) stage_init(b->E.stage, most);
   b->E.csweeps = probs[0].coarse_sweeps;
   off = 0;
   for (int i = 0; i < n && rc == BP_OK; ++i) {
@@ -2715,7 +2889,6 @@ bp_status bp_batch_get_fields(bp_batch* b, int32_t i, double* eta, double* p, do
     if (step) *step = b->P[i].step;
     return fail(BP_ERR_DIVERGED, "the problem diverged and left the batch");
   }
-  if (!b->E.probs.empty()) BPCHK(extract_fields(b->E));
   return fields_of(b->E, b->P[i], eta, p, sigma, step);
 }
 
@@ -2779,6 +2952,7 @@ bp_status bp_server_create(void* device_ws, size_t ws_bytes, void* hip_stream, i
     delete s;
     return rc;
   }
+  stage_init(s->E.stage, Stage::kSlots * Stage::kSlot);  // requests of any size
   s->pool.init(area, ws_bytes - area);
   *out = s;
   return BP_OK;
@@ -2880,7 +3054,6 @@ bp_status bp_server_advance(bp_server* s, int32_t nsteps, int32_t* n_active, int
     for (SrvReq* r : s->active)
       if (r->P.step >= r->nsteps) done.push_back(r);
     if (done.empty()) continue;
-    BPCHK(extract_fields(s->E));
     for (SrvReq* r : done) {
       const size_t N = (size_t)r->P.nx * r->P.ny;
       r->eta.resize(2 * N);

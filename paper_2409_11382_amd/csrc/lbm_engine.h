@@ -115,6 +115,15 @@ struct CellL {    // per-cell kernels over the finest level
   const int* need;    // as in SweepL
 };
 
+struct ExtractL {  // fields of some rows of one problem, as dense planes
+  const ProbD* prob;
+  double *eta, *p, *sig;  // 2, 1 (or none) and 3 planes, `stride` values apart
+  int64_t stride;
+  double c0;
+  int row0, rows;
+  int* flags;  // set: [0] to 1 on a non-finite displacement (else left), [1] to the problem's flag
+};
+
 struct ProbL {    // one block per problem
   const ProbD* probs;
   const int* pids;
@@ -244,7 +253,7 @@ hipError_t launch_rebase(const CellL& a, int ntiles, hipStream_t s);
 template <typename T>
 hipError_t launch_rebase_force(const CellL& a, int ntiles, hipStream_t s);
 template <typename T, bool SHIFT>
-hipError_t launch_extract(const CellL& a, int ntiles, hipStream_t s);
+hipError_t launch_extract(const ExtractL& a, int nx, hipStream_t s);
 
 // levels >= 2 stored in FP64 (dbl) or FP32; level 1 is FP64 in both
 hipError_t launch_tail(const TailL& a, int nprobs, bool dbl, hipStream_t s);

@@ -1274,30 +1274,41 @@ __global__ __launch_bounds__(256) void k_rebase(CellL a) {
   if (FORCE) force_finish<T>(P, V, c, n, central, sst, sp);
 }
 
-// displacement and stress of the current populations (eqs. displacement,
-// moments:bared); stress in physical units
+// displacement, pressure and stress of the current populations (eqs.
+// displacement, moments:bared; stress in physical units) for rows row0 ..
+// row0 + rows - 1, as dense planes.  The output may be host memory that the
+// device maps: the link to the host then bounds the launch, and writing there
+// leaves out a copy.  D of a block's 66 x 6 region is formed once per cell.
 template <typename T, bool SHIFT>
-__global__ __launch_bounds__(256) void k_extract(CellL a) {
-  const int2 te = a.tiles[blockIdx.x];
-  const ProbD& P = a.probs[te.x];
+__global__ __launch_bounds__(256) void k_extract(ExtractL a) {
+  __shared__ double sD[kFRY][kFRX];
+  const ProbD& P = *a.prob;
   const LevelD& V = P.lv[P.L];
-  const CellPos c = cell_pos(V, te.y);
-  if (!c.in) return;
   const T* g = (const T*)V.gA;
   const bool perx = P.el[kLeft] == kElPeriodic, pery = P.el[kBottom] == kElPeriodic;
-  double D[3][3];
-  for (int dy = -1; dy <= 1; ++dy)
-    for (int dx = -1; dx <= 1; ++dx) {
-      const int xs = ghost_map(c.x + dx, V.nx, perx), ys = ghost_map(c.y + dy, V.ny, pery);
-      const int64_t k = (int64_t)ys * V.pitch + xs;
-      T u[8];
-      for (int q = 0; q < 8; ++q) u[q] = g[q * V.plane + k];
-      D[dy + 1][dx + 1] = P.kD * double(el_ms(u));
-    }
-  double gx, gy;
+  const int cbx = (V.nx + kCellBX - 1) / kCellBX;
+  const int x0 = (int)(blockIdx.x % cbx) * kCellBX, y0 = a.row0 + (int)(blockIdx.x / cbx) * kCellBY;
+  for (int r = threadIdx.x; r < kFRX * kFRY; r += blockDim.x) {
+    const int rx = r % kFRX, ry = r / kFRX;
+    const int x = x0 - 1 + rx, y = y0 - 1 + ry;
+    if (x > V.nx || y > V.ny) continue;  // no cell of the grid reads farther
+    const int64_t k = (int64_t)ghost_map(y, V.ny, pery) * V.pitch + ghost_map(x, V.nx, perx);
+    T u[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) u[q] = g[q * V.plane + k];
+    sD[ry][rx] = P.kD * double(el_ms(u));
+  }
+  __syncthreads();
+  if (a.flags && blockIdx.x == 0 && threadIdx.x == 0) a.flags[1] = P.flags[0];
+  const int x = x0 + (int)(threadIdx.x % kCellBX), row = y0 - a.row0 + (int)(threadIdx.x / kCellBX);
+  const int y = a.row0 + row;
+  if (x >= V.nx || row >= a.rows || y >= V.ny) return;
+  double D[3][3], gx, gy;
+  force_gather(sD, D);
   grad_c(D, gx, gy);
-  const int64_t idx = (int64_t)c.y * V.pitch + c.x;
+  const int64_t idx = (int64_t)y * V.pitch + x;
   double u[8];
+#pragma unroll
   for (int q = 0; q < 8; ++q) u[q] = double(g[q * V.plane + idx]);
   const T* Ft = (const T*)P.Ft;
   const double Fx = double(Ft[idx]) + P.cstar * gx, Fy = double(Ft[V.plane + idx]) + P.cstar * gy;
@@ -1310,13 +1321,16 @@ __global__ __launch_bounds__(256) void k_extract(CellL a) {
     m10 += P.ref64 ? ((const double*)P.eref)[idx] : double(((const float*)P.eref)[idx]);
     m01 += P.ref64 ? ((const double*)P.eref)[V.plane + idx] : double(((const float*)P.eref)[V.plane + idx]);
   }
-  const int64_t o = (int64_t)c.y * V.nx + c.x, N = (int64_t)V.nx * V.ny;
-  P.eta[o] = m10 + 0.5 * Fx;
-  P.eta[N + o] = m01 + 0.5 * Fy;
+  const int64_t o = (int64_t)row * V.nx + x, N = a.stride;
+  const double ex = m10 + 0.5 * Fx, ey = m01 + 0.5 * Fy;
+  a.eta[o] = ex;
+  a.eta[N + o] = ey;
   const double bs = P.b_s * ms, bd = P.b_d * md, b11 = P.b_d * m11;
-  P.sig[o] = -0.5 * (bs + bd) * P.inv_c0h;
-  P.sig[N + o] = -b11 * P.inv_c0h;
-  P.sig[2 * N + o] = -0.5 * (bs - bd) * P.inv_c0h;
+  a.sig[o] = -0.5 * (bs + bd) * P.inv_c0h;
+  a.sig[N + o] = -b11 * P.inv_c0h;
+  a.sig[2 * N + o] = -0.5 * (bs - bd) * P.inv_c0h;
+  if (a.p) a.p[o] = P.pout[idx] / a.c0;
+  if (a.flags && !(isfinite(ex) && isfinite(ey))) a.flags[0] = 1;
 }
 
 template <typename T>
@@ -1344,9 +1358,10 @@ hipError_t launch_rebase_force(const CellL& a, int ntiles, hipStream_t s) {
   return hipGetLastError();
 }
 template <typename T, bool SHIFT>
-hipError_t launch_extract(const CellL& a, int ntiles, hipStream_t s) {
-  if (ntiles <= 0) return hipSuccess;
-  hipLaunchKernelGGL((k_extract<T, SHIFT>), dim3(ntiles), dim3(256), 0, s, a);
+hipError_t launch_extract(const ExtractL& a, int nx, hipStream_t s) {
+  const int blocks = ((nx + kCellBX - 1) / kCellBX) * ((a.rows + kCellBY - 1) / kCellBY);
+  if (blocks <= 0) return hipSuccess;
+  hipLaunchKernelGGL((k_extract<T, SHIFT>), dim3(blocks), dim3(256), 0, s, a);
   return hipGetLastError();
 }
 
@@ -2605,9 +2620,9 @@ template hipError_t launch_rebase<float>(const CellL&, int, hipStream_t);
 template hipError_t launch_rebase<double>(const CellL&, int, hipStream_t);
 template hipError_t launch_rebase_force<float>(const CellL&, int, hipStream_t);
 template hipError_t launch_rebase_force<double>(const CellL&, int, hipStream_t);
-template hipError_t launch_extract<float, false>(const CellL&, int, hipStream_t);
-template hipError_t launch_extract<float, true>(const CellL&, int, hipStream_t);
-template hipError_t launch_extract<double, false>(const CellL&, int, hipStream_t);
-template hipError_t launch_extract<double, true>(const CellL&, int, hipStream_t);
+template hipError_t launch_extract<float, false>(const ExtractL&, int, hipStream_t);
+template hipError_t launch_extract<float, true>(const ExtractL&, int, hipStream_t);
+template hipError_t launch_extract<double, false>(const ExtractL&, int, hipStream_t);
+template hipError_t launch_extract<double, true>(const ExtractL&, int, hipStream_t);
 
 }  // namespace biot

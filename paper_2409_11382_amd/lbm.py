@@ -266,9 +266,9 @@ class Solver:
 
     def fields(self):
         p = self.p
-        eta = np.zeros((2, p.ny, p.nx))
-        pr = np.zeros((p.ny, p.nx))
-        sig = np.zeros((3, p.ny, p.nx))
+        eta = np.empty((2, p.ny, p.nx))
+        pr = np.empty((p.ny, p.nx))
+        sig = np.empty((3, p.ny, p.nx))
         st = C.c_int32(0)
         _check(self._lib.bp_get_fields(self._h, _dptr(eta), _dptr(pr), _dptr(sig), C.byref(st)),
                "bp_get_fields")
@@ -438,9 +438,9 @@ class Batch:
 
     def fields(self, i):
         p = self.problems[i]
-        eta = np.zeros((2, p.ny, p.nx))
-        pr = np.zeros((p.ny, p.nx))
-        sig = np.zeros((3, p.ny, p.nx))
+        eta = np.empty((2, p.ny, p.nx))
+        pr = np.empty((p.ny, p.nx))
+        sig = np.empty((3, p.ny, p.nx))
         st = C.c_int32(0)
         _check(self._lib.bp_batch_get_fields(self._h, int(i), _dptr(eta), _dptr(pr), _dptr(sig), C.byref(st)),
                "bp_batch_get_fields")
@@ -505,9 +505,9 @@ class Server:
 
     def result(self, ticket: int):
         nx, ny = self._shape[ticket]
-        eta = np.zeros((2, ny, nx))
-        p = np.zeros((ny, nx))
-        sig = np.zeros((3, ny, nx))
+        eta = np.empty((2, ny, nx))
+        p = np.empty((ny, nx))
+        sig = np.empty((3, ny, nx))
         rc = self._lib.bp_server_result(self._h, int(ticket), _dptr(eta), _dptr(p), _dptr(sig))
         if rc != BP_ERR_STATE:  # the library forgets the ticket unless it is still running
             self._shape.pop(ticket, None)
