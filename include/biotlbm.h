@@ -241,6 +241,9 @@ bp_status bp_stats(const bp_solver *s, bp_run_stats *st);
  *   four applications with the restriction on 32 x 32 regions
  *                                    if cells <= quad_res_narrow_max_cells
  *                                    (else on 64 x 32 regions)
+ * A bound at its initial value (256^2, 512^2 and 128^2 cells for quad, tall
+ * and narrow) leaves the choice to the blocks the depth's launches would have:
+ * the shape whose blocks take the cheaper rounds on the chip.
  * bp_autotune searches the bounds by coordinate descent: each bound in turn
  * takes the value among five candidates whose time steps run fastest on this
  * engine (HIP events, `steps` steps per candidate after one warm-up step; a

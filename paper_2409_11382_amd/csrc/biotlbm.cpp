@@ -686,19 +686,13 @@ int set_apps(int set) {
 // restriction sweep's pass over the populations (the 256-problem batch and
 // the 2048^2 strip step about 4% faster than with a separate sweep there)
 constexpr int64_t kFuseResCells = int64_t(1) << 40;
-// a depth whose launches cover at most this many cells in all takes four
-// applications per launch: the launch is bound by the dependent work of one
-// block, and its 32 x 32 regions (16 x 16 outputs) put 256 blocks on the 256
-// CUs at 256^2 cells; the redundant halo work costs little there
-// (BIOT_QUAD_MAX_CELLS overrides the bound)
+// bounds on the cells a depth covers in all (bp_tuning, and the environment
+// variables BIOT_QUAD_MAX_CELLS and BIOT_TALL_MAX_CELLS) for four applications
+// per launch, the narrow region of four with the restriction, and the tall
+// regions of pairs.  A bound left at its value here yields to the block counts
+// of region_rules() below.
 constexpr int64_t kQuadMaxCells = 256 * 256;
-// above this many cells in all, a depth's launch of four applications with
-// the restriction takes the 64-column regions: 12 x 12 outputs of the narrow
-// region would need about two blocks per CU there
 constexpr int64_t kQuadNarrowResCells = 128 * 128;
-// a depth of at most this many cells in all takes pairs on tall regions (one
-// block per CU); larger ones keep two 8-wave blocks per CU, which hide each
-// other's barrier waits (BIOT_TALL_MAX_CELLS overrides the bound)
 constexpr int64_t kTallMaxCells = 512 * 512;
 struct DepthLists {
   int off[8][3] = {};
@@ -707,6 +701,7 @@ struct DepthLists {
   bool fres = false;  // restriction fused into the last pre-smoothing launch
   bool qwide = false; // its four-application form on 64-column regions
   bool tall = false;  // pairs on tall regions
+  bool rtall = false; // pairs with the restriction on tall regions
   int tail_off = 0, tail_cnt = 0;  // problems whose coarse tail starts here
 };
 
@@ -813,7 +808,66 @@ void xcd_order(std::vector<int2>& tiles, size_t off) {
 bool quad_at(const Engine& E, int d) { return E.depth[d].quad && !(d == 0 && E.fdbl && E.shift); }
 // the alternative region for A applications per launch at depth d
 bool alt_at(const Engine& E, int d, int A) {
-  return (A == 2 || A == 3) ? E.depth[d].tall : (A == 5 && E.depth[d].qwide);
+  return A == 2 ? E.depth[d].tall : (A == 3 ? E.depth[d].rtall : (A == 5 && E.depth[d].qwide));
+}
+
+// blocks of a depth's launches of A applications
+int64_t depth_blocks(const Engine& E, int d, int A, bool alt) {
+  int64_t n = 0;
+  for (const Prob* P : E.probs) {
+    const int l = P->L - d, td = P->lo.tail_depth;
+    if (l < 1 || (td > 0 && d >= td)) continue;
+    const LevelLay& v = P->lo.lv[l];
+    n += sweepn_tiles(v.nx, v.ny, v.dbl, A, E.shift && d == 0, alt);
+  }
+  return n;
+}
+
+// Launch shapes of a depth.  A launch lasts as many rounds as its blocks fill
+// the chip's 256 CUs, so where a bound was not given the region with the
+// cheaper rounds is taken.  Measured times in us of one launch at n^2 cells:
+// - four applications on 32 x 32 regions: two blocks' rounds (at most 512
+//   blocks, and 256 with the restriction) against two pairs.  320^2: 17.1 for
+//   four, 23.2 for two pairs, with the restriction 17.6 against 27.6; 368^2,
+//   in a third and second round: 21.6 and 23.2, 27.9 and 27.8.
+// - four with the restriction: narrow regions in one round (184 x 120 cells
+//   in 160 blocks: a 736 x 480 step 555, on wide ones 566), wide beyond (224^2
+//   in 361 narrow blocks: an 896^2 step 786, wide 778).
+// - pairs in FP32 shifted storage: a round of tall regions (one block per CU)
+//   takes about 8.6 after the first 5.5, a round of the default (two per CU)
+//   10.7 after 7.  512^2: 14.3 against 17.1; 640^2 21.8, 18.5; 736^2 23.4,
+//   25.0; 1024^2 38.8, 35.7.
+// - pairs in FP32: both regions have the same outputs; one per CU while one
+//   round suffices (512^2 12.8, two per CU 14.4), else two (1024^2 37.4, 32.0).
+// - pairs in FP64: tall where that is one round and the default more than one
+//   (512^2 17.5 against 21.6; 320^2 16.2, 12.2; 1024^2 52.8, 44.1).
+// - pairs with the restriction: in FP32 likewise (shifted 512^2 19.2 against
+//   21.2, 384^2 18.3, 16.5, 1024^2 53.6, 48.5); in FP64 rounds of 16 waves x 2
+//   rows cost 8/9 of those of 12 x 3 (384^2 20.3 and 23.2; 512^2 31.3, 23.6;
+//   640^2 35.8, 39.1; 736^2 48.1, 43.0).
+void region_rules(const Engine& E, int d, int64_t cells, DepthLists& r) {
+  const bool shift = E.shift && d == 0;
+  auto rounds = [&](int A, bool alt, int per_cu) {
+    const int64_t slots = 256 * per_cu;
+    return (depth_blocks(E, d, A, alt) + slots - 1) / slots;
+  };
+  r.quad = cells <= E.quad_max_cells;
+  if (E.quad_max_cells == kQuadMaxCells) r.quad = r.quad || (rounds(4, false, 2) <= 1 && rounds(5, true, 1) <= 1);
+  r.quad = r.quad && E.quad;
+  r.qwide = cells > E.qnarrow_max_cells;
+  if (E.qnarrow_max_cells == kQuadNarrowResCells) r.qwide = r.qwide && rounds(5, false, 1) > 1;
+  r.tall = r.rtall = cells <= E.tall_max_cells;
+  if (E.tall_max_cells != kTallMaxCells) return;
+  if (E.fdbl) {
+    r.tall = rounds(2, false, 2) > 1 && rounds(2, true, 1) <= 1;
+    r.rtall = 8 * rounds(3, false, 1) > 9 * rounds(3, true, 1);
+  } else if (shift) {
+    r.tall = 55 + 86 * rounds(2, true, 1) <= 70 + 107 * rounds(2, false, 2);
+    r.rtall = rounds(3, true, 1) <= 1 && rounds(3, false, 1) > 1;
+  } else {
+    r.tall = rounds(2, true, 1) <= 1;
+    r.rtall = rounds(3, true, 1) <= 1;
+  }
 }
 
 // write descriptors and tile lists for the current problem set
@@ -841,10 +895,8 @@ bp_status engine_upload(Engine& E) {
       const int l = P.L - d, td = P.lo.tail_depth;
       if (l >= 1 && !(td > 0 && d >= td)) depth_cells += (int64_t)P.lo.lv[l].nx * P.lo.lv[l].ny;
     }
-    E.depth[d].quad = E.quad && depth_cells <= E.quad_max_cells;
     E.depth[d].fres = E.fuse_res && depth_cells <= E.fres_max_cells;
-    E.depth[d].qwide = depth_cells > E.qnarrow_max_cells;
-    E.depth[d].tall = depth_cells <= E.tall_max_cells;
+    region_rules(E, d, depth_cells, E.depth[d]);
     for (size_t i = 0; i < np; ++i) {  // tiles along x of the level at this depth, by its A = 5 width
       const int l = E.probs[i]->L - d;
       if (l >= 1) set_tiles_x(pd[i].lv[l], 5, sweepn_tiles_x(E.probs[i]->lo.lv[l].nx, 5, alt_at(E, d, 5)));

@@ -182,8 +182,8 @@ hipError_t launch_tsweep(const SweepL& a, int ntiles, hipStream_t s);
 // (four, then the restricted residual).  A region is COLS x (WAVES NK 64/COLS)
 // cells with NK row indices per wave, each covering 64/COLS rows of COLS
 // cells; a tile has (COLS - 4 A) x (rows - 4 A) outputs.  Each A has a
-// default region and, chosen per depth by the cells it covers in all, an
-// alternative (ALT):
+// default region and, chosen per depth by the rounds its blocks take on the
+// chip (region_rules), an alternative (ALT):
 // - pairs, with or without the restriction, take 64-cell rows.  By default 8
 //   waves of 3 rows (FP32 without shifted storage: 4, whose LDS then still
 //   fits two blocks; FP64: 2): two blocks share a CU and hide each other's
@@ -191,6 +191,9 @@ hipError_t launch_tsweep(const SweepL& a, int ntiles, hipStream_t s);
 //   fill the chip about once: tall regions of 32 rows (16 waves x 2) and 36
 //   rows (12 waves x 3), 24 output rows, one block per CU on a 512^2 level and
 //   less halo work; FP64 shifted storage lacks the LDS and keeps 8 waves.
+//   FP64 with the restriction has LDS for one block per CU in either form: 16
+//   waves x 2 rows, 20 output rows (1024^2: 77 us, ALT 76; 8 waves x 3 rows,
+//   which left the SIMDs two waves each, took 89).
 // - four applications are used only on depths of few cells, where the launch
 //   is bound by the dependent work of one block: a 32 x 32 region (16 x 16
 //   outputs) spreads such a depth over about four times as many compute units
@@ -199,10 +202,12 @@ hipError_t launch_tsweep(const SweepL& a, int ntiles, hipStream_t s);
 //   serves the larger of those depths.
 template <typename T, bool SHIFT, int A, bool ALT>
 __host__ __device__ constexpr int sweepn_waves() {
+  if (A == 3 && sizeof(T) == 8 && !SHIFT) return ALT ? 12 : 16;
   return A >= 4 ? 16 : ((!ALT || (sizeof(T) == 8 && SHIFT)) ? 8 : (A == 2 ? 16 : 12));
 }
 template <typename T, bool SHIFT, int A, bool ALT>
 __host__ __device__ constexpr int sweepn_rows() {
+  if (A == 3 && sizeof(T) == 8 && !SHIFT) return ALT ? 3 : 2;
   return A >= 4 ? ((A == 5 && ALT) ? 2 : 1)
                 : ((sizeof(T) == 4 && !SHIFT && !ALT) ? 4
                                                       : (A == 3 ? 3 : ((ALT && !(sizeof(T) == 8 && SHIFT)) ? 2 : (sizeof(T) == 8 ? 2 : 3))));

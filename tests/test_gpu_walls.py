@@ -98,3 +98,24 @@ def test_smallest_levels_as_a_matrix(lbm, shape, walls, sweeps):
     print(shape, walls, sweeps, e, errs, flush=True)
     assert e < 1e-11
     assert all(v < tol for v, tol in errs)
+
+
+@pytest.mark.parametrize("prec,tol", [("fp64", 1e-10), ("fp32_shifted", 1e-5)])
+@pytest.mark.parametrize("nx,ny", [(512, 250), (530, 250), (640, 400)])
+def test_regions_chosen_by_their_rounds(lbm, nx, ny, prec, tol):
+    """Sizes at the lines between launch shapes: 512 blocks of four
+    applications and more, one and two rounds of the pairs' regions; the
+    chosen shapes and the pairs' default regions against the oracle."""
+    p = _problem("DTSD", nx, ny)
+    o = Oracle(p, threads=oracle_threads())
+    o.step(1)
+    B = o.fields()
+    for bounds in ({}, dict(quad_max_cells=0, tall_max_cells=0, quad_res_narrow_max_cells=0)):
+        s = lbm.Solver(p, prec)
+        if bounds:
+            s.set_tuning(bounds)
+        s.step(1)
+        A = s.fields()
+        s.close()
+        e = {k: rel(A[k], B[k]) for k in ("eta", "p")}
+        assert max(e.values()) <= tol, (nx, ny, prec, bounds, e)
