@@ -540,6 +540,7 @@ bp_status setup_problem(const bp_problem* p, const Layout& lo, char* base, hipSt
   d.norm2 = (double*)(base + lo.off_scal);
   d.phase = (int*)(base + lo.off_scal + 32);
   d.flags = (int*)(base + lo.off_scal + 40);
+  d.arrived = (int*)(base + lo.off_scal + 80);
   d.ad = (int*)(base + lo.off_scal + 48);
   d.ad_ratio = (double*)(base + lo.off_scal + 56);  // right after ad: one read for both
   d.gref = (double*)(base + lo.off_scal + 64);
@@ -594,6 +595,7 @@ bp_status setup_problem(const bp_problem* p, const Layout& lo, char* base, hipSt
     const bool used = (p->side[k].el == BP_EL_DIRICHLET || p->side[k].el == BP_EL_TRACTION);
     d.elbc[k] = used ? elbc : nullptr;
     d.ftype[k] = ftype;
+    if (k == kLeft || k == kBottom) d.fper[k == kBottom] = ty[0] == kFlPeriodic;
     d.flbc[k] = flbc;
   }
   d.addt = nullptr;
@@ -644,7 +646,7 @@ bp_status setup_problem(const bp_problem* p, const Layout& lo, char* base, hipSt
 }
 
 // ---------------------------------------------------------------- engine
-enum OpKind { OP_SWEEP, OP_TAIL, OP_FORCE, OP_REBASE_EL, OP_REBASE_FORCE, OP_AD_RESET, OP_FLOW, OP_FINALIZE, OP_ADVANCE, OP_INIT };
+enum OpKind { OP_SWEEP, OP_TAIL, OP_FORCE, OP_REBASE_EL, OP_REBASE_FORCE, OP_AD_RESET, OP_FLOW, OP_FINALIZE, OP_INIT };
 
 struct Op {
   OpKind kind;
@@ -743,7 +745,7 @@ struct Engine {
   int* d_div = nullptr;   // divergence flags by problem index (k_finalize)
   size_t tiles_cap = 0, probs_cap = 0;
   std::vector<DepthLists> depth;  // per depth
-  int fine_off = 0, fine_cnt = 0; // depth-0 full-set tiles of every problem (flow)
+  int fine_off = 0, fine_cnt = 0; // flow tiles of every problem
   int cell_off = 0, cell_cnt = 0; // finest-level cell blocks
   int init_off = 0, init_cnt = 0; // cell blocks of the problems still to initialise
   std::vector<Op> step_ops;
@@ -938,8 +940,11 @@ bp_status engine_upload(Engine& E) {
   E.fine_off = (int)tiles.size();
   for (size_t i = 0; i < np; ++i) {
     const Prob& P = *E.probs[i];
-    const int nt = sweep_tiles(P.nx, P.ny);
-    for (int t = 0; t < nt; ++t) tiles.push_back(make_int2((int)i, t));
+    LevelD& D = pd[i].lv[P.L];
+    set_tiles_x(D, 1, flow_tiles_x(P.nx));
+    const int nt = flow_tiles(P.nx, P.ny);
+    for (int t = 0; t < nt; ++t)
+      tiles.push_back(make_int2((int)i, t / D.tiles_xn[1] << D.tile_shift[1] | t % D.tiles_xn[1]));
   }
   if (E.xcd_order) xcd_order(tiles, E.fine_off);
   E.fine_cnt = (int)tiles.size() - E.fine_off;
@@ -1217,17 +1222,14 @@ void build_step_ops(Engine& E, std::vector<Op>& ops) {
       cur ^= 1;
     }
   }
-  ops.push_back(flow_op(E));
-  if (E.ne > 0) {
-    // the norms of the last post-smoothing launch (the flow step leaves them
-    // alone), then the step counter, in one launch
-    Op f = prob_op(E, OP_FINALIZE);
-    f.pl.fused = (E.fuse && E.K >= 2 && !E.lag) ? 1 : 0;  // the last post-smoothing launch was multi-application
-    f.pl.advance = 1;
-    ops.push_back(f);
-  } else {
-    ops.push_back(prob_op(E, OP_ADVANCE));
-  }
+  // the flow step; its last block adds up the norms of the last post-smoothing
+  // launch (the flow step leaves them alone) and counts the step.  In a launch
+  // of their own these took 4.4 us of a 512^2 step and the launch's gap.
+  Op f = flow_op(E);
+  f.cl.finish = E.ne > 0 ? 1 : 2;
+  f.cl.fused = (E.fuse && E.K >= 2 && !E.lag) ? 1 : 0;  // the last post-smoothing launch was multi-application
+  f.cl.div = E.d_div;
+  ops.push_back(f);
 }
 
 // the multi-application launch of an op: applications per launch, then the
@@ -1281,7 +1283,6 @@ hipError_t run_op(const Engine& E, const Op& o) {
     case OP_TAIL: return launch_tail(o.tl, o.count, E.fdbl, s);
     case OP_FINALIZE: return launch_finalize(o.pl, o.count, s);
     case OP_AD_RESET: return launch_ad_reset(o.pl, s);
-    case OP_ADVANCE: return launch_advance(o.pl, o.count, s);
   }
   return hipSuccess;
 }
@@ -1625,7 +1626,7 @@ bp_status build_adaptive(Engine& E) {
     }
   }
   E.ad_ops[AD_END].push_back(flow_op(E));
-  E.ad_ops[AD_END].push_back(prob_op(E, OP_ADVANCE));
+  E.ad_ops[AD_END].back().cl.finish = 2;
   if (!full) {
     E.ad_ops[AD_END_G] = E.ad_ops[AD_END];
     set_need(E.ad_ops[AD_END_G], P.d.ad);
@@ -2103,7 +2104,6 @@ std::string op_name(const Op& o) {
     case OP_REBASE_EL: return "rebase displacement";
     case OP_REBASE_FORCE: return "rebase+force";
     case OP_FINALIZE: return "finalize";
-    case OP_ADVANCE: return "advance";
     case OP_AD_RESET: return "adaptive reset";
     case OP_INIT: return "initial conditions";
   }

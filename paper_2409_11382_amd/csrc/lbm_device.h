@@ -57,16 +57,16 @@ __device__ __forceinline__ int wrap_index(int i, int n, int reach) {
 
 // ------------------------------------------------------------- global memory
 // pointers known to be global (descriptors hold them, so the compiler cannot
-// tell and would take flat instructions), addressed by a scalar base and a
-// 32-bit byte offset per lane
+// tell and would take flat instructions), addressed by a scalar base and an
+// unsigned byte offset per lane, of 32 bits where a plane allows
 template <typename T> using GPtr = __attribute__((address_space(1))) T*;
 template <typename T> __device__ __forceinline__ GPtr<T> gptr(const void* p) {
   return (GPtr<T>)(uintptr_t)p;
 }
-template <typename T> __device__ __forceinline__ T gload(GPtr<T> base, uint32_t off) {
+template <typename T, typename Off> __device__ __forceinline__ T gload(GPtr<T> base, Off off) {
   return *(GPtr<T>)((GPtr<char>)base + off);
 }
-template <typename T> __device__ __forceinline__ void gstore(GPtr<T> base, uint32_t off, T v) {
+template <typename T, typename Off> __device__ __forceinline__ void gstore(GPtr<T> base, Off off, T v) {
   *(GPtr<T>)((GPtr<char>)base + off) = v;
 }
 

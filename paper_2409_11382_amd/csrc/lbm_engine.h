@@ -17,6 +17,9 @@ namespace biot {
 
 constexpr int kMaxLevels = 16;
 constexpr int kTileY = 12;              // output rows of a sweep tile (even: 2x2 restriction pairs)
+// flow tile: 8 waves of 2 rows, one halo row and column on each side
+constexpr int kFlowWaves = 8, kFlowRows = 2;
+constexpr int kFlowTileX = 62, kFlowTileY = kFlowWaves * kFlowRows - 2;
 constexpr int kCellBX = 64, kCellBY = 4;  // per-cell kernels: 64 x 4 cells per block
 
 enum SweepMode : int { kSmooth = 0, kRestrict = 1, kApply = 2 };
@@ -28,7 +31,8 @@ struct LevelD {
   int nx, ny, pitch;
   uint32_t inv_nx;   // ceil(2^20 / nx): rows of cells below 1024 without a division
   int tiles_x;       // sweep tiles along x: ceil(nx / kTileX)
-  int tiles_xn[6];   // multi-application sweep tiles along x, by applications per launch (2..5)
+  int tiles_xn[6];   // multi-application sweep tiles along x, by applications per launch (2..5);
+                     // [1]: flow tiles
   int tile_shift[6]; // their entries hold tile row << shift | tile column
   int dbl;           // FP64 storage
   int64_t plane;
@@ -41,6 +45,7 @@ struct ProbD {
   int el[4];                  // elastic side types
   const double* elbc[4];      // finest level: 8 additive terms per boundary cell (or null)
   const int8_t* ftype[4];     // flow type per boundary cell
+  int fper[2];                // flow periodic in x, in y
   const double* flbc[4];      // 9 additive terms per boundary cell
   void* f[2];                 // flow populations, ping-pong by step parity
   double* D[3];               // D^n rotated by step number mod 3
@@ -61,6 +66,7 @@ struct ProbD {
   double* norm2;              // finalized sums
   int* phase;                 // completed steps (device copy)
   int* flags;                 // [0] non-finite seen
+  int* arrived;               // blocks of the flow step that have ended (0 between launches)
   int* ad;                    // adaptive cycles: [0] stop (1 converged or at N_E,max, 2 non-finite), [1] cycles done
   double* ad_ratio;           // adaptive cycles: the last measured ||g - S(g)|| / ||g||
   double om_s, om_d, beta22, kD, cstar, gamma;
@@ -113,6 +119,11 @@ struct CellL {    // per-cell kernels over the finest level
   const int2* tiles;  // (problem, cell block)
   const int* skip;    // as in SweepL
   const int* need;    // as in SweepL
+  // flow step: what a problem's last block does: 0 nothing, 1 the norms of the
+  // step (as ProbL with advance) and the step counter, 2 the step counter
+  int finish;
+  int fused;          // finish 1: as in ProbL
+  int* div;           // finish 1: as in ProbL
 };
 
 struct ExtractL {  // fields of some rows of one problem, as dense planes
@@ -273,11 +284,12 @@ hipError_t launch_finalize(const ProbL& a, int nprobs, hipStream_t s);
 // adaptive cycles on the device: reset the stop flag and count for a step
 // (the stopping test itself follows the norms in k_finalize)
 hipError_t launch_ad_reset(const ProbL& a, hipStream_t s);
-hipError_t launch_advance(const ProbL& a, int nprobs, hipStream_t s);
 hipError_t launch_copy(void* dst, const void* src, size_t bytes, hipStream_t s);
 hipError_t launch_fill_zero(void* dst, size_t bytes, hipStream_t s);
 
 inline int sweep_tiles_x(int nx) { return (nx + kTileX - 1) / kTileX; }
+inline int flow_tiles_x(int nx) { return (nx + kFlowTileX - 1) / kFlowTileX; }
+inline int flow_tiles(int nx, int ny) { return flow_tiles_x(nx) * ((ny + kFlowTileY - 1) / kFlowTileY); }
 inline int sweep_tiles(int nx, int ny) { return sweep_tiles_x(nx) * ((ny + kTileY - 1) / kTileY); }
 inline int sweepn_tiles_x(int nx, int apps, bool alt) {
   return (nx + sweepn_tile_x(apps, alt) - 1) / sweepn_tile_x(apps, alt);

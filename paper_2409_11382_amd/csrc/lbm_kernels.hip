@@ -875,17 +875,97 @@ hipError_t launch_tsweep2(const SweepL& a, int ntiles, bool ref64, hipStream_t s
   return hipGetLastError();
 }
 
+// fixed-order FP64 sum of the finest level's norm partials of problem pid and
+// what follows from it, by the first 256 threads of a block (all take part in
+// the barriers)
+__device__ __forceinline__ void finalize_norms(const ProbL& a, int pid, double* sr, double* sg) {
+  const ProbD& P = a.probs[pid];
+  double r = 0.0, g = 0.0;
+  const int n = a.fused == 2 ? P.ntiles_test : (a.fused ? P.ntiles_fine2 : P.ntiles_fine);
+  const double2* part = (const double2*)(a.fused ? P.partials2 : P.partials);
+  // each thread sums the pairs k = t, t + 256, ... in that order; eight loads
+  // are in flight at a time (an absent pair adds +0, which leaves the sums of
+  // squares unchanged)
+  for (int k0 = threadIdx.x; k0 < n && threadIdx.x < 256; k0 += 8 * 256) {
+    double2 v[8];
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      const int k = k0 + 256 * u;
+      v[u] = k < n ? part[k] : make_double2(0.0, 0.0);
+    }
+#pragma unroll
+    for (int u = 0; u < 8; ++u) {
+      r += v[u].x;
+      g += v[u].y;
+    }
+  }
+  if (threadIdx.x < 256) {
+    sr[threadIdx.x] = r;
+    sg[threadIdx.x] = g;
+  }
+  __syncthreads();
+  for (int o = 128; o > 0; o >>= 1) {
+    if ((int)threadIdx.x < o) {
+      sr[threadIdx.x] += sr[threadIdx.x + o];
+      sg[threadIdx.x] += sg[threadIdx.x + o];
+    }
+    __syncthreads();
+  }
+  if (threadIdx.x == 0) {
+    P.norm2[0] = sr[0];
+    P.norm2[1] = sg[0];
+    // divergence: a non-finite norm, or (at the end of a fixed-cycle step)
+    // ||g|| grown above 1e8 times the largest of its first kGrowthWindow
+    // non-zero step-end values since the initial conditions.  The window
+    // keeps a first value at rounding level (loads that cancel at t = 0)
+    // from becoming the reference.
+    if (!isfinite(sr[0]) || !isfinite(sg[0])) P.flags[0] = 1;
+    if (a.advance && isfinite(sg[0]) && sg[0] > 0.0) {
+      double* gr = P.gref;
+      if (gr[1] < kGrowthWindow) {
+        gr[0] = fmax(gr[0], sg[0]);
+        gr[1] += 1.0;
+      } else if (sg[0] > 1e16 * gr[0]) {
+        P.flags[0] = 1;
+      }
+    }
+    if (a.div && P.flags[0]) a.div[pid] = 1;
+    if (a.advance) *P.phase += 1;
+    if (a.decide && !P.ad[0]) {
+      // the host's stopping test of the adaptive schedule, in the same FP64
+      // steps: stop, or count the cycle that follows
+      const double nr = sqrt(sr[0]), ng = sqrt(sg[0]);
+      P.ad_ratio[0] = ng > 0 ? nr / ng : 0.0;
+      if (!isfinite(nr) || !isfinite(ng))
+        P.ad[0] = 2;
+      else if (nr <= a.tol * ng || P.ad[1] >= a.ne_max)
+        P.ad[0] = 1;
+      else
+        P.ad[1] += 1;
+    }
+  }
+}
+
 // ======================================================================
 // flow step: D^n, centred coupling source (eq. source:implicit), pressure
 // (eq. pressure), SRT collision with source (eqs. pressure:collision,
-// pressure:collision:source), pull-stream and boundary rules
+// pressure:collision:source), pull-stream and boundary rules; then, by the
+// last block of a problem to end, the step's norms and counter (a.finish)
 // ======================================================================
+// Bound by memory on large grids and by one block's chain of loads on small
+// ones: every load of both rows of a lane is issued before the first use, from
+// offsets without branches (ghost cells are copies: an index), and 8 waves of
+// 2 rows keep more loads in flight than 4 of 4.  Types of wall cells are read in
+// tiles that hold a wall.  With the norms' launch of its own, before -> now:
+// 64^2 20 -> 12 us, 512^2 23.6 -> 17.4, 2048^2 149 -> 132 (144 bytes per cell,
+// 4.6 TB/s), 1024^2 in FP64 66 -> 55.
 template <typename T, bool SHIFT>
-__global__ __launch_bounds__(256) void k_tflow(CellL a) {
+__global__ __launch_bounds__((kWave * kFlowWaves)) void k_tflow(CellL a) {
   if (gated_off(a.skip, a.need)) return;  // uniform over the grid
-  constexpr int TY = kTileY;
-  constexpr int RR = TY + 2;                 // one halo row each side
-  constexpr int NK = (RR + 3) / 4;
+  constexpr int NW = kFlowWaves, NK = kFlowRows;
+  constexpr int RR = NW * NK;                // one halo row each side
+  constexpr int TY = kFlowTileY;
+  using Off = uint64_t;  // offsets of 32 bits are no faster here
   __shared__ T sF[9][RR][kWave];
   __shared__ double sPd[SHIFT ? RR : 1][kWave];  // pressure reference, FP64 or FP32 (same bytes)
   float (*sPf)[kWave] = reinterpret_cast<float (*)[kWave]>(sPd);
@@ -895,82 +975,78 @@ __global__ __launch_bounds__(256) void k_tflow(CellL a) {
   const LevelD& V = P.lv[P.L];
   const int nx = V.nx, ny = V.ny, pitch = V.pitch;
   const int64_t plane = V.plane;
-  const int tx = te.y % V.tiles_x, ty = te.y / V.tiles_x;
+  const int sh = V.tile_shift[1];
+  const int tx = te.y & ((1 << sh) - 1), ty = te.y >> sh;
   const int lane = threadIdx.x & (kWave - 1), w = threadIdx.x / kWave;
-  const int x = tx * kTileX - kHalo + lane;
+  const int x = tx * kFlowTileX - 1 + lane;
   const int y0 = ty * TY;
   const int n = *P.phase;
-  const T* fin = (const T*)P.f[n & 1];
-  T* fout = (T*)P.f[(n + 1) & 1];
-  const double* D1 = P.D[(n + 2) % 3];
-  const double* D2 = P.D[(n + 1) % 3];
-  double* Dn = P.D[n % 3];
-  const T* g = (const T*)V.gA;
-  const bool perx = P.ftype[kLeft][0] == kFlPeriodic;
-  const bool pery = P.ftype[kBottom][0] == kFlPeriodic;
-  const bool col_ok = x >= -1 && x < nx + 1;
-  const int gx = col_ok ? ghost_map(x, nx, perx) : 0;
-  const bool out_lane = lane >= kHalo && lane < kWave - kHalo && x < nx;
-  void* pref = SHIFT ? P.pref[n & 1] : nullptr;
+  const GPtr<T> fin = gptr<T>(P.f[n & 1]), fout = gptr<T>(P.f[(n + 1) & 1]), g = gptr<T>(V.gA);
+  const GPtr<double> D1 = gptr<double>(P.D[(n + 2) % 3]), D2 = gptr<double>(P.D[(n + 1) % 3]);
+  const GPtr<double> Dn = gptr<double>(P.D[n % 3]), pout = gptr<double>(P.pout);
+  const GPtr<double> src = gptr<double>(P.src), omf = gptr<double>(P.omf);
+  const bool has_src = P.src != nullptr, has_omf = P.omf != nullptr;
+  const bool perx = P.fper[0] != 0, pery = P.fper[1] != 0;
+  const int gx = perx ? wrap_index(x, nx, kWave) : clampi(x, 0, nx - 1);
+  const bool out_lane = lane >= 1 && lane < kWave - 1 && x < nx;
+  const void* pref = SHIFT ? P.pref[n & 1] : nullptr;
   void* pref_next = SHIFT ? P.pref[(n + 1) & 1] : nullptr;
   const bool r64 = P.ref64 != 0;
 
+  T f[NK][9], gg[NK][8];
+  double d1[NK], d2[NK], sc[NK], om_[NK], pr[NK];
+  Off cell[NK];
 #pragma unroll
   for (int kk = 0; kk < NK; ++kk) {
-    const int j = w + 4 * kk;
-    if (j >= RR) continue;
-    const int y = y0 - 1 + j;
-    const bool ok = col_ok && y >= -1 && y < ny + 1;
-    T f[9];
-    T s = T(0), om = T(P.omf_u);
-    double pr = 0.0;
+    const int y = y0 - 1 + w + NW * kk;
+    const int gy = pery ? wrap_index(y, ny, RR) : clampi(y, 0, ny - 1);
+    cell[kk] = (Off)gy * (Off)pitch + (Off)gx;
 #pragma unroll
-    for (int i = 0; i < 9; ++i) f[i] = T(0);
-    if (ok) {
-      const int gy = ghost_map(y, ny, pery);
-      const int64_t idx = (int64_t)gy * pitch + gx;
+    for (int i = 0; i < 9; ++i) f[kk][i] = gload(fin + i * plane, cell[kk] * (Off)sizeof(T));
 #pragma unroll
-      for (int i = 0; i < 9; ++i) f[i] = fin[i * plane + idx];
-      T gg[8];
+    for (int q = 0; q < 8; ++q) gg[kk][q] = gload(g + q * plane, cell[kk] * (Off)sizeof(T));
+    d1[kk] = gload(D1, cell[kk] * 8);
+    d2[kk] = gload(D2, cell[kk] * 8);
+    sc[kk] = has_src ? gload(src, cell[kk] * 8) : 0.0;
+    om_[kk] = has_omf ? gload(omf, cell[kk] * 8) : P.omf_u;
+    pr[kk] = !SHIFT ? 0.0
+                    : (r64 ? gload(gptr<double>(pref), cell[kk] * 8) : double(gload(gptr<float>(pref), cell[kk] * 4)));
+  }
 #pragma unroll
-      for (int q = 0; q < 8; ++q) gg[q] = g[q * plane + idx];
-      const double dn = P.kD * double(el_ms(gg));
-      const double d1 = D1[idx], d2 = D2[idx];
-      double sv = -P.alpha_h * ((1.0 - P.r) * (d1 - d2) + P.r * (dn - d1));
-      if (P.src) sv += P.src[idx];
-      s = T(sv);
-      if (P.omf) om = T(P.omf[idx]);
-      if (SHIFT) pr = r64 ? ((const double*)pref)[idx] : double(((const float*)pref)[idx]);
-      if (out_lane && j >= 1 && j <= TY && y < ny) {
-        Dn[idx] = dn;
-        T sum = T(0);
-#pragma unroll
-        for (int i = 0; i < 9; ++i) sum += f[i];
-        P.pout[idx] = double(sum) + 0.5 * sv + pr;
-      }
-    }
+  for (int kk = 0; kk < NK; ++kk) {
+    const int j = w + NW * kk;
+    const double dn = P.kD * double(el_ms(gg[kk]));
+    double sv = -P.alpha_h * ((1.0 - P.r) * (d1[kk] - d2[kk]) + P.r * (dn - d1[kk]));
+    if (has_src) sv += sc[kk];
+    const T s = T(sv), om = T(om_[kk]);
     T p = T(0);
 #pragma unroll
-    for (int i = 0; i < 9; ++i) p += f[i];
+    for (int i = 0; i < 9; ++i) p += f[kk][i];
+    if (out_lane && j >= 1 && j <= TY && y0 - 1 + j < ny) {
+      gstore(Dn, cell[kk] * 8, dn);
+      gstore(pout, cell[kk] * 8, double(p) + 0.5 * sv + pr[kk]);
+    }
     p += T(0.5) * s;
     const T so = (T(1) - T(0.5) * om) * s;
 #pragma unroll
     for (int i = 0; i < 9; ++i) {
       const T wi = T(w9(i));
-      sF[i][j][lane] = f[i] - om * (f[i] - wi * p) + wi * so;
+      sF[i][j][lane] = f[kk][i] - om * (f[kk][i] - wi * p) + wi * so;
     }
     if (SHIFT) {
       if (r64)
-        sPd[j][lane] = pr;
+        sPd[j][lane] = pr[kk];
       else
-        sPf[j][lane] = float(pr);
+        sPf[j][lane] = float(pr[kk]);
     }
   }
   __syncthreads();
 
+  // does the tile hold a wall cell?
+  const bool bnd = (!perx && (tx == 0 || (tx + 1) * kFlowTileX >= nx)) || (!pery && (ty == 0 || y0 + TY >= ny));
 #pragma unroll
   for (int kk = 0; kk < NK; ++kk) {
-    const int j = w + 4 * kk;
+    const int j = w + NW * kk;
     if (j < 1 || j > TY) continue;
     const int y = y0 - 1 + j;
     const bool valid = out_lane && y < ny;
@@ -990,8 +1066,11 @@ __global__ __launch_bounds__(256) void k_tflow(CellL a) {
       for (int i = 1; i < 9; ++i) fo[i] += T(float(w9(i)) * (sPf[j - cy9(i)][lane - cx9(i)] - p0f));
     }
     auto pn = [&](int jj, int ll) { return r64 ? sPd[jj][ll] : double(sPf[jj][ll]); };
-    const int tL = P.ftype[kLeft][y], tR = P.ftype[kRight][y];
-    const int tB = P.ftype[kBottom][x], tT = P.ftype[kTop][x];
+    int tL = kFlPeriodic, tR = kFlPeriodic, tB = kFlPeriodic, tT = kFlPeriodic;
+    if (bnd) {
+      tL = P.ftype[kLeft][y], tR = P.ftype[kRight][y];
+      tB = P.ftype[kBottom][x], tT = P.ftype[kTop][x];
+    }
     const bool wl = x == 0 && tL != kFlPeriodic;
     const bool wr = x == nx - 1 && tR != kFlPeriodic;
     const bool wb = y == 0 && tB != kFlPeriodic;
@@ -1046,7 +1125,7 @@ __global__ __launch_bounds__(256) void k_tflow(CellL a) {
         fo[i] = v;
       }
     }
-    const int64_t idx = (int64_t)y * pitch + x;
+    const Off idx = (Off)y * (Off)pitch + (Off)x;
     if (SHIFT) {
       // the next step's re-base of the pressure: its zeroth moment moves into
       // the reference, written to the other buffer (neighbours of this launch
@@ -1057,19 +1136,46 @@ __global__ __launch_bounds__(256) void k_tflow(CellL a) {
 #pragma unroll
       for (int i = 0; i < 9; ++i) fo[i] -= T(w9(i)) * pl;
       if (r64)
-        ((double*)pref_next)[idx] = p0 + double(pl);
+        gstore(gptr<double>(pref_next), idx * 8, p0 + double(pl));
       else
-        ((float*)pref_next)[idx] = float(p0) + float(pl);
+        gstore(gptr<float>(pref_next), idx * 4, float(p0) + float(pl));
     }
 #pragma unroll
-    for (int i = 0; i < 9; ++i) fout[i * plane + idx] = fo[i];
+    for (int i = 0; i < 9; ++i) gstore(fout + i * plane, idx * (Off)sizeof(T), fo[i]);
+  }
+
+  // the last block of the problem to end: every other has read the step
+  // counter, and the norms' partials come from an earlier launch
+  if (a.finish) {
+    __shared__ int last;
+    __syncthreads();  // sF is free
+    if (threadIdx.x == 0) {
+      const int blocks = V.tiles_xn[1] * ((ny + TY - 1) / TY);
+      last = atomicAdd(P.arrived, 1) == blocks - 1;
+    }
+    __syncthreads();
+    if (last) {
+      if (threadIdx.x == 0) *P.arrived = 0;
+      if (a.finish == 1) {
+        ProbL p{};
+        p.probs = a.probs;
+        p.fused = a.fused;
+        p.advance = 1;
+        p.div = a.div;
+        double* sr = reinterpret_cast<double*>(&sF[0][0][0]);
+        finalize_norms(p, te.x, sr, sr + 256);
+      } else if (threadIdx.x == 0) {
+        *P.phase += 1;
+      }
+    }
   }
 }
+
 
 template <typename T, bool SHIFT>
 hipError_t launch_tflow(const CellL& a, int ntiles, hipStream_t s) {
   if (ntiles <= 0) return hipSuccess;
-  hipLaunchKernelGGL((k_tflow<T, SHIFT>), dim3(ntiles), dim3(256), 0, s, a);
+  hipLaunchKernelGGL((k_tflow<T, SHIFT>), dim3(ntiles), dim3(kWave * kFlowWaves), 0, s, a);
   return hipGetLastError();
 }
 
@@ -1220,6 +1326,7 @@ __global__ __launch_bounds__(256) void k_init(CellL a) {
   if (te.y == 0 && threadIdx.x == 0) {
     *P.phase = 0;
     P.flags[0] = 0;
+    *P.arrived = 0;
     P.gref[0] = 0.0;
     P.gref[1] = 0.0;
   }
@@ -2469,78 +2576,10 @@ hipError_t launch_tail(const TailL& a, int nprobs, bool dbl, hipStream_t s) {
 // ======================================================================
 // per-problem kernels
 // ======================================================================
-// fixed-order FP64 sum of the finest level's norm partials
 __global__ __launch_bounds__(256) void k_finalize(ProbL a) {
   if (gated_off(a.skip, a.need)) return;  // uniform over the grid
-  const ProbD& P = a.probs[a.pids[blockIdx.x]];
   __shared__ double sr[256], sg[256];
-  double r = 0.0, g = 0.0;
-  const int n = a.fused == 2 ? P.ntiles_test : (a.fused ? P.ntiles_fine2 : P.ntiles_fine);
-  const double2* part = (const double2*)(a.fused ? P.partials2 : P.partials);
-  // each thread sums the pairs k = t, t + 256, ... in that order; eight loads
-  // are in flight at a time (an absent pair adds +0, which leaves the sums of
-  // squares unchanged)
-  for (int k0 = threadIdx.x; k0 < n; k0 += 8 * 256) {
-    double2 v[8];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int k = k0 + 256 * u;
-      v[u] = k < n ? part[k] : make_double2(0.0, 0.0);
-    }
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      r += v[u].x;
-      g += v[u].y;
-    }
-  }
-  sr[threadIdx.x] = r;
-  sg[threadIdx.x] = g;
-  __syncthreads();
-  for (int o = 128; o > 0; o >>= 1) {
-    if ((int)threadIdx.x < o) {
-      sr[threadIdx.x] += sr[threadIdx.x + o];
-      sg[threadIdx.x] += sg[threadIdx.x + o];
-    }
-    __syncthreads();
-  }
-  if (threadIdx.x == 0) {
-    P.norm2[0] = sr[0];
-    P.norm2[1] = sg[0];
-    // divergence: a non-finite norm, or (at the end of a fixed-cycle step)
-    // ||g|| grown above 1e8 times the largest of its first kGrowthWindow
-    // non-zero step-end values since the initial conditions.  The window
-    // keeps a first value at rounding level (loads that cancel at t = 0)
-    // from becoming the reference.
-    if (!isfinite(sr[0]) || !isfinite(sg[0])) P.flags[0] = 1;
-    if (a.advance && isfinite(sg[0]) && sg[0] > 0.0) {
-      double* gr = P.gref;
-      if (gr[1] < kGrowthWindow) {
-        gr[0] = fmax(gr[0], sg[0]);
-        gr[1] += 1.0;
-      } else if (sg[0] > 1e16 * gr[0]) {
-        P.flags[0] = 1;
-      }
-    }
-    if (a.div && P.flags[0]) a.div[a.pids[blockIdx.x]] = 1;
-    if (a.advance) *P.phase += 1;
-    if (a.decide && !P.ad[0]) {
-      // the host's stopping test of the adaptive schedule, in the same FP64
-      // steps: stop, or count the cycle that follows
-      const double nr = sqrt(sr[0]), ng = sqrt(sg[0]);
-      P.ad_ratio[0] = ng > 0 ? nr / ng : 0.0;
-      if (!isfinite(nr) || !isfinite(ng))
-        P.ad[0] = 2;
-      else if (nr <= a.tol * ng || P.ad[1] >= a.ne_max)
-        P.ad[0] = 1;
-      else
-        P.ad[1] += 1;
-    }
-  }
-}
-
-__global__ void k_advance(ProbL a) {
-  if (gated_off(a.skip, a.need)) return;
-  if (threadIdx.x == 0) *a.probs[a.pids[blockIdx.x]].phase += 1;
+  finalize_norms(a, a.pids[blockIdx.x], sr, sg);
 }
 
 __global__ __launch_bounds__(256) void k_copy(uint4* dst, const uint4* src, size_t n16) {
@@ -2570,12 +2609,6 @@ hipError_t launch_ad_reset(const ProbL& a, hipStream_t s) {
 hipError_t launch_finalize(const ProbL& a, int nprobs, hipStream_t s) {
   if (nprobs <= 0) return hipSuccess;
   hipLaunchKernelGGL(k_finalize, dim3(nprobs), dim3(256), 0, s, a);
-  return hipGetLastError();
-}
-
-hipError_t launch_advance(const ProbL& a, int nprobs, hipStream_t s) {
-  if (nprobs <= 0) return hipSuccess;
-  hipLaunchKernelGGL(k_advance, dim3(nprobs), dim3(64), 0, s, a);
   return hipGetLastError();
 }
 

@@ -119,3 +119,23 @@ def test_regions_chosen_by_their_rounds(lbm, nx, ny, prec, tol):
         s.close()
         e = {k: rel(A[k], B[k]) for k in ("eta", "p")}
         assert max(e.values()) <= tol, (nx, ny, prec, bounds, e)
+
+
+@pytest.mark.parametrize("walls", ["DTSD", "TSDT", "PPDT", "SDPP"])
+@pytest.mark.parametrize("nx,ny", [(5, 3), (62, 14), (63, 15), (125, 29)])
+def test_flow_tiles(lbm, walls, nx, ny):
+    """The flow step's tiles (62 x 14 outputs): smaller than, exactly and one
+    more than a tile, and a ragged last tile, on every wall type; the step
+    counter and norms follow from its last block over several steps."""
+    p = _problem(walls, nx, ny).replace(levels=1)
+    o = Oracle(p, threads=oracle_threads())
+    o.step(4)
+    B = o.fields()
+    for prec, tol in (("fp64", 1e-10), ("fp32_shifted", 1e-5)):
+        s = lbm.Solver(p, prec)
+        s.step(4)
+        A = s.fields()
+        n = s.stats()["step"]
+        s.close()
+        e = {k: rel(A[k], B[k]) for k in ("eta", "p")}
+        assert n == 4 and max(e.values()) <= tol, (walls, nx, ny, prec, e)
