@@ -499,6 +499,7 @@ bp_status setup_problem(const bp_problem* p, const Layout& lo, char* base, hipSt
     d.lv[l].ny = v.ny;
     d.lv[l].inv_nx = ((1u << 20) + (uint32_t)v.nx - 1) / (uint32_t)v.nx;
     d.lv[l].pitch = v.pitch;
+    d.lv[l].toff = l > 1 ? d.lv[l - 1].toff + lo.lv[l - 1].nx * lo.lv[l - 1].ny : 0;
     d.lv[l].tiles_x = sweep_tiles_x(v.nx);
     for (int A = 2; A <= 5; ++A) set_tiles_x(d.lv[l], A, sweepn_tiles_x(v.nx, A, false));  // A = 5: set per depth
     d.lv[l].dbl = v.dbl ? 1 : 0;
@@ -551,7 +552,7 @@ bp_status setup_problem(const bp_problem* p, const Layout& lo, char* base, hipSt
   if (lo.tail_depth > 0) {
     size_t o = 0;
     for (int l = 1; l <= (lo.full_tail ? lo.L : lo.L - lo.tail_depth); ++l) {
-      HIPCHK(launch_tail_tables(d.el, lo.lv[l].nx, lo.lv[l].ny, d.ttab + o, st));
+      HIPCHK(launch_tail_tables(d.el, lo.lv[l].nx, lo.lv[l].ny, lo.lv[l].dbl ? 8 : 4, d.ttab + o, st));
       o += (size_t)8 * lo.lv[l].nx * lo.lv[l].ny;
     }
   }

@@ -63,6 +63,11 @@ template <typename T> using GPtr = __attribute__((address_space(1))) T*;
 template <typename T> __device__ __forceinline__ GPtr<T> gptr(const void* p) {
   return (GPtr<T>)(uintptr_t)p;
 }
+// an object that no kernel writes (the descriptors): its loads are scalar and
+// may be moved over stores and barriers
+template <typename T> __device__ __forceinline__ const T& constant(const T* p) {
+  return *(const T*)(const __attribute__((address_space(4))) T*)(uintptr_t)p;
+}
 template <typename T, typename Off> __device__ __forceinline__ T gload(GPtr<T> base, Off off) {
   return *(GPtr<T>)((GPtr<char>)base + off);
 }

@@ -35,6 +35,7 @@ struct LevelD {
                      // [1]: flow tiles
   int tile_shift[6]; // their entries hold tile row << shift | tile column
   int dbl;           // FP64 storage
+  int toff;          // coarse tail: cells of the levels below (its gather table's place in ttab)
   int64_t plane;
 };
 
@@ -273,9 +274,9 @@ hipError_t launch_extract(const ExtractL& a, int nx, hipStream_t s);
 
 // levels >= 2 stored in FP64 (dbl) or FP32; level 1 is FP64 in both
 hipError_t launch_tail(const TailL& a, int nprobs, bool dbl, hipStream_t s);
-// gather tables of one coarse-tail level (nx * ny <= kTailThreads) for the
-// elastic side types el[4]
-hipError_t launch_tail_tables(const int* el, int nx, int ny, uint32_t* out, hipStream_t s);
+// gather tables of one coarse-tail level (nx * ny <= kTailThreads, values of sz
+// bytes) for the elastic side types el[4]
+hipError_t launch_tail_tables(const int* el, int nx, int ny, int sz, uint32_t* out, hipStream_t s);
 // the matrix of the V-cycle of levels top..1 from zero (K smoothing steps),
 // tail_matrix_bytes(cells of level top) bytes at out
 hipError_t launch_tail_matrix(const ProbD& P, int top, int K, double* out, hipStream_t s);

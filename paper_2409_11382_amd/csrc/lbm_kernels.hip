@@ -1526,8 +1526,8 @@ hipError_t launch_extract(const ExtractL& a, int nx, hipStream_t s) {
 // (x, y) as plus or minus one post-collision value of the level: interior and
 // periodic pulls, mirror images at symmetry walls, bounce-back (Dirichlet) and
 // anti-bounce-back (traction).  The code returned is that value's index in sG
-// (q-major, dense: q * n + y * nx + x) with bit 15 set for a minus sign.
-__device__ __forceinline__ uint32_t tail_pull_code(const int q, int x, int y, int nx, int ny, const int* el, int n) {
+// (q-major: q * ps + y * nx + x) with bit 15 set for a minus sign.
+__device__ __forceinline__ uint32_t tail_pull_code(const int q, int x, int y, int nx, int ny, const int* el, int ps) {
   const int cx = cx8(q), cy = cy8(q);
   int sx = x - cx, sy = y - cy;
   const bool perx = el[kLeft] == kElPeriodic, pery = el[kBottom] == kElPeriodic;
@@ -1540,33 +1540,36 @@ __device__ __forceinline__ uint32_t tail_pull_code(const int q, int x, int y, in
     sy = (sy + ny) % ny;
     oy = false;
   }
-  if (!ox && !oy) return (uint32_t)(q * n + sy * nx + sx);
+  if (!ox && !oy) return (uint32_t)(q * ps + sy * nx + sx);
   const int elx = cx > 0 ? el[kLeft] : el[kRight];
   const int ely = cy > 0 ? el[kBottom] : el[kTop];
   bool usex;
   if (ox && oy) {
-    if (elx == kElSymmetry && ely == kElSymmetry) return (uint32_t)(opp8(q) * n + y * nx + x);
+    if (elx == kElSymmetry && ely == kElSymmetry) return (uint32_t)(opp8(q) * ps + y * nx + x);
     usex = ely == kElSymmetry;
   } else if (ox) {
-    if (elx == kElSymmetry) return (uint32_t)(mx8(q) * n + sy * nx + x);
+    if (elx == kElSymmetry) return (uint32_t)(mx8(q) * ps + sy * nx + x);
     usex = true;
   } else {
-    if (ely == kElSymmetry) return (uint32_t)(my8(q) * n + y * nx + sx);
+    if (ely == kElSymmetry) return (uint32_t)(my8(q) * ps + y * nx + sx);
     usex = false;
   }
-  const uint32_t o = (uint32_t)(opp8(q) * n + y * nx + x);
+  const uint32_t o = (uint32_t)(opp8(q) * ps + y * nx + x);
   return (usex ? elx : ely) == kElDirichlet ? o : (o | 0x8000u);
 }
 
 // per-cell gather tables of a level: the 8 neighbours of the D(g) stencil
-// (mirror ghosts at walls) and the 8 pull codes, 16 bits each
+// (mirror ghosts at walls) and the 8 populations pulled, as 16-bit byte offsets
+// into the level's planes in LDS (planes of `ps` cells of sz bytes), ready as
+// LDS addresses.  An offset is a multiple of 4, so the two low bits of a word of
+// pulls hold the signs of its lower and upper one (anti-bounce-back).
 struct TailTab {
   uint32_t dn[4], pl[4];
+  bool neg;  // a pull of this wave changes sign (tail_tab_signs)
 };
 
-__device__ __forceinline__ TailTab tail_table(const int* el, int c, int nx, int ny) {
+__device__ __forceinline__ TailTab tail_table(const int* el, int c, int nx, int ny, uint32_t sz, uint32_t ps) {
   TailTab tb;
-  const int n = nx * ny;
   const int x = c % nx, y = c / nx;
   const bool perx = el[kLeft] == kElPeriodic, pery = el[kBottom] == kElPeriodic;
   uint32_t d[8];
@@ -1575,17 +1578,52 @@ __device__ __forceinline__ TailTab tail_table(const int* el, int c, int nx, int 
   for (int dy = -1; dy <= 1; ++dy)
 #pragma unroll
     for (int dx = -1; dx <= 1; ++dx)
-      if (dx != 0 || dy != 0) d[k++] = (uint32_t)(ghost_map(y + dy, ny, pery) * nx + ghost_map(x + dx, nx, perx));
+      if (dx != 0 || dy != 0) d[k++] = sz * (uint32_t)(ghost_map(y + dy, ny, pery) * nx + ghost_map(x + dx, nx, perx));
 #pragma unroll
   for (int j = 0; j < 4; ++j) {
     tb.dn[j] = d[2 * j] | (d[2 * j + 1] << 16);
-    tb.pl[j] = tail_pull_code(2 * j, x, y, nx, ny, el, n) | (tail_pull_code(2 * j + 1, x, y, nx, ny, el, n) << 16);
+    const uint32_t lo = tail_pull_code(2 * j, x, y, nx, ny, el, ps), hi = tail_pull_code(2 * j + 1, x, y, nx, ny, el, ps);
+    tb.pl[j] = (lo & 0x7fffu) * sz | (lo >> 15) | (hi >> 15) << 1 | ((hi & 0x7fffu) * sz) << 16;
   }
+  tb.neg = false;
   return tb;
+}
+__device__ __forceinline__ void tail_tab_signs(TailTab& tb) {
+  tb.neg = __any(((tb.pl[0] | tb.pl[1] | tb.pl[2] | tb.pl[3]) & 3u) != 0);
 }
 
 __device__ __forceinline__ uint32_t lo16(uint32_t w) { return w & 0xffffu; }
 __device__ __forceinline__ uint32_t hi16(uint32_t w) { return w >> 16; }
+template <typename T> __device__ __forceinline__ T tail_at(const T* base, uint32_t off) {
+  return *(const T*)((const char*)base + off);
+}
+// population q as pulled through the table
+template <typename T> __device__ __forceinline__ T tail_pull(const TailTab& tb, const T* sG, int q) {
+  const uint32_t w = tb.pl[q >> 1];
+  T v = tail_at(sG, (q & 1) ? hi16(w) : w & 0xfffcu);
+  if (tb.neg) {
+    const uint32_t flip = (q & 1) ? (w << 30) & 0x80000000u : w << 31;
+    if constexpr (sizeof(T) == 8)
+      v = __builtin_bit_cast(T, __builtin_bit_cast(uint64_t, v) ^ (uint64_t)flip << 32);
+    else
+      v = __builtin_bit_cast(T, __builtin_bit_cast(uint32_t, v) ^ flip);
+  }
+  return v;
+}
+// central gradient of D at this thread's cell
+template <typename T> __device__ __forceinline__ void tail_grad(const TailTab& tb, const T* sD, T& gx, T& gy) {
+  T v[3][3];
+  v[0][0] = tail_at(sD, lo16(tb.dn[0]));
+  v[0][1] = tail_at(sD, hi16(tb.dn[0]));
+  v[0][2] = tail_at(sD, lo16(tb.dn[1]));
+  v[1][0] = tail_at(sD, hi16(tb.dn[1]));
+  v[1][2] = tail_at(sD, lo16(tb.dn[2]));
+  v[2][0] = tail_at(sD, hi16(tb.dn[2]));
+  v[2][1] = tail_at(sD, lo16(tb.dn[3]));
+  v[2][2] = tail_at(sD, hi16(tb.dn[3]));
+  v[1][1] = T(0);  // the centred gradient does not use the centre
+  grad_c(v, gx, gy);
+}
 
 template <typename T>
 __device__ __forceinline__ ElConst<T> tail_consts(const ProbD& P) {
@@ -1599,57 +1637,37 @@ __device__ __forceinline__ ElConst<T> tail_consts(const ProbD& P) {
   return k;
 }
 
-// one application of S on a whole level held by the workgroup: thread t owns
-// cells t, t + 1024, ...; G (iterate) and R (right-hand side) in registers,
-// gathers through the level's tables.  blend: G <- (1 - gamma) G + gamma S(G);
-// otherwise G <- G - S(G) (residual).  Two barriers; sD and sG may be reused
-// right after the return.
-template <typename T, int NC>
-__device__ __forceinline__ void tail_relax(const ElConst<T>& k, int n, const TailTab (&tb)[NC], T (&G)[NC][8],
-                                           const T (&R)[NC][8], T* sD, T* sG, bool blend) {
-  const int t = threadIdx.x;
-#pragma unroll
-  for (int c4 = 0; c4 < NC; ++c4) {
-    const int c = t + kTailThreads * c4;
-    if (c < n) sD[c] = k.kD * el_ms(G[c4]);
-  }
+// one application of S on a whole level held by the workgroup: thread c owns
+// cell c; G (iterate) and R (right-hand side) in registers, gathers through the
+// level's tables.  blend: G <- (1 - gamma) G + gamma S(G); otherwise
+// G <- G - S(G) (residual).  Two barriers; sD and sG may be reused right after
+// the return.  sG's planes have PS cells whatever the level, so that planes and
+// tables are LDS addresses as they stand (50 of a sweep's 170 vector
+// instructions were address arithmetic and unpacking; FP64 tail 42.0 -> 40.5 us).
+template <typename T, int PS = kTailThreads>
+__device__ __forceinline__ void tail_relax(const ElConst<T>& k, int n, const TailTab& tb, T (&G)[1][8],
+                                           const T (&R)[1][8], T* sD, T* sG, bool blend) {
+  const int c = threadIdx.x;
+  if (c < n) sD[c] = k.kD * el_ms(G[0]);
   __syncthreads();
-#pragma unroll
-  for (int c4 = 0; c4 < NC; ++c4) {
-    const int c = t + kTailThreads * c4;
-    if (c >= n) continue;
-    T v[3][3];
-    v[0][0] = sD[lo16(tb[c4].dn[0])];
-    v[0][1] = sD[hi16(tb[c4].dn[0])];
-    v[0][2] = sD[lo16(tb[c4].dn[1])];
-    v[1][0] = sD[hi16(tb[c4].dn[1])];
-    v[1][2] = sD[lo16(tb[c4].dn[2])];
-    v[2][0] = sD[hi16(tb[c4].dn[2])];
-    v[2][1] = sD[lo16(tb[c4].dn[3])];
-    v[2][2] = sD[hi16(tb[c4].dn[3])];
-    v[1][1] = T(0);  // the centred gradient does not use the centre
+  if (c < n) {
     T gx_, gy_;
-    grad_c(v, gx_, gy_);
+    tail_grad(tb, sD, gx_, gy_);
     T u[8], s8[8];
 #pragma unroll
-    for (int q = 0; q < 8; ++q) u[q] = G[c4][q] - R[c4][q];
+    for (int q = 0; q < 8; ++q) u[q] = G[0][q] - R[0][q];
     // a blending sweep streams gamma times the post-collision populations
     el_collide(u, k.cstar * gx_, k.cstar * gy_, k, s8, blend ? k.gamma : T(1));
 #pragma unroll
-    for (int q = 0; q < 8; ++q) sG[q * n + c] = s8[q];
+    for (int q = 0; q < 8; ++q) sG[q * PS + c] = s8[q];
   }
   __syncthreads();
   const T omg = T(1) - k.gamma;
-#pragma unroll
-  for (int c4 = 0; c4 < NC; ++c4) {
-    const int c = t + kTailThreads * c4;
-    if (c >= n) continue;
+  if (c < n) {
 #pragma unroll
     for (int q = 0; q < 8; ++q) {
-      const uint32_t code = (q & 1) ? hi16(tb[c4].pl[q >> 1]) : lo16(tb[c4].pl[q >> 1]);
-      const T v = sG[code & 0x7fffu];
-      const T gi = (code & 0x8000u) ? -v : v;
-      G[c4][q] = blend ? omg * G[c4][q] + gi : G[c4][q] - gi;
+      const T gi = tail_pull(tb, sG, q);
+      G[0][q] = blend ? omg * G[0][q] + gi : G[0][q] - gi;
     }
   }
 }
@@ -1657,7 +1675,7 @@ __device__ __forceinline__ void tail_relax(const ElConst<T>& k, int n, const Tai
 // the first smoothing application of a zero iterate: D(g) = 0, so the
 // collision of -R needs no neighbour.  One barrier; sG is read until the next.
 template <typename T>
-__device__ __forceinline__ void tail_first(const ElConst<T>& k, int n, const TailTab (&tb)[1], T (&G)[1][8],
+__device__ __forceinline__ void tail_first(const ElConst<T>& k, int n, const TailTab& tb, T (&G)[1][8],
                                            const T (&R)[1][8], T* sG) {
   const int c = threadIdx.x;
   if (c < n) {
@@ -1666,16 +1684,12 @@ __device__ __forceinline__ void tail_first(const ElConst<T>& k, int n, const Tai
     for (int q = 0; q < 8; ++q) u[q] = -R[0][q];
     el_collide(u, T(0), T(0), k, s8, k.gamma);
 #pragma unroll
-    for (int q = 0; q < 8; ++q) sG[q * n + c] = s8[q];
+    for (int q = 0; q < 8; ++q) sG[q * kTailThreads + c] = s8[q];
   }
   __syncthreads();
   if (c < n) {
 #pragma unroll
-    for (int q = 0; q < 8; ++q) {
-      const uint32_t code = (q & 1) ? hi16(tb[0].pl[q >> 1]) : lo16(tb[0].pl[q >> 1]);
-      const T v = sG[code & 0x7fffu];
-      G[0][q] = (code & 0x8000u) ? -v : v;
-    }
+    for (int q = 0; q < 8; ++q) G[0][q] = tail_pull(tb, sG, q);
   } else {
 #pragma unroll
     for (int q = 0; q < 8; ++q) G[0][q] = T(0);
@@ -1683,41 +1697,35 @@ __device__ __forceinline__ void tail_first(const ElConst<T>& k, int n, const Tai
 }
 
 // the gather tables of level l (built once at setup by k_tail_tables)
-__device__ __forceinline__ const uint4* tail_tab_ptr(const ProbD& P, int l) {
-  size_t o = 0;
-  for (int m = 1; m < l; ++m) o += (size_t)P.lv[m].nx * P.lv[m].ny;
-  return (const uint4*)(P.ttab + 8 * o);
+// (threads without a cell take the last one's)
+__device__ __forceinline__ void tail_tab_load(const ProbD& P, int l, int c, TailTab& tb) {
+  const uint4* t = (const uint4*)(P.ttab + 8 * (size_t)P.lv[l].toff) + 2 * min(c, P.lv[l].nx * P.lv[l].ny - 1);
+  const uint4 a = t[0], b = t[1];
+  tb.dn[0] = a.x;
+  tb.dn[1] = a.y;
+  tb.dn[2] = a.z;
+  tb.dn[3] = a.w;
+  tb.pl[0] = b.x;
+  tb.pl[1] = b.y;
+  tb.pl[2] = b.z;
+  tb.pl[3] = b.w;
+  tb.neg = false;
 }
 
-__device__ __forceinline__ void tail_tab_load(const ProbD& P, int l, int c, TailTab (&tb)[1]) {
-  if (c < P.lv[l].nx * P.lv[l].ny) {
-    const uint4* t = tail_tab_ptr(P, l) + 2 * c;
-    const uint4 a = t[0], b = t[1];
-    tb[0].dn[0] = a.x;
-    tb[0].dn[1] = a.y;
-    tb[0].dn[2] = a.z;
-    tb[0].dn[3] = a.w;
-    tb[0].pl[0] = b.x;
-    tb[0].pl[1] = b.y;
-    tb[0].pl[2] = b.z;
-    tb[0].pl[3] = b.w;
-  }
-}
-
-__global__ __launch_bounds__(kTailThreads) void k_tail_tables(int4 el4, int nx, int ny, uint32_t* out) {
+__global__ __launch_bounds__(kTailThreads) void k_tail_tables(int4 el4, int nx, int ny, int sz, uint32_t* out) {
   const int c = threadIdx.x;
   if (c >= nx * ny) return;
   const int el[4] = {el4.x, el4.y, el4.z, el4.w};
-  const TailTab tb = tail_table(el, c, nx, ny);
+  const TailTab tb = tail_table(el, c, nx, ny, (uint32_t)sz, kTailThreads);
   uint4* o = (uint4*)(out + 8 * c);
   o[0] = make_uint4(tb.dn[0], tb.dn[1], tb.dn[2], tb.dn[3]);
   o[1] = make_uint4(tb.pl[0], tb.pl[1], tb.pl[2], tb.pl[3]);
 }
 
-hipError_t launch_tail_tables(const int* el, int nx, int ny, uint32_t* out, hipStream_t s) {
+hipError_t launch_tail_tables(const int* el, int nx, int ny, int sz, uint32_t* out, hipStream_t s) {
   if (nx * ny > kTailThreads) return hipErrorInvalidValue;
   hipLaunchKernelGGL(k_tail_tables, dim3(1), dim3(kTailThreads), 0, s, make_int4(el[0], el[1], el[2], el[3]), nx, ny,
-                     out);
+                     sz, out);
   return hipGetLastError();
 }
 
@@ -1773,19 +1781,23 @@ __device__ __forceinline__ void tail_small(const ProbD& P, int top, int K, const
                                            double* keep, double* lds) {
   const int c = threadIdx.x;
   const ElConst<double> k = tail_consts<double>(P);
-  TailTab tb[1];
+  TailTab tb{};
   double R[1][8];
 #pragma unroll
   for (int q = 0; q < 8; ++q) R[0][q] = R0[0][q];
   constexpr int N = kTailDenseCells;
+  auto table = [&](int l) {
+    if (c < P.lv[l].nx * P.lv[l].ny) tb = tail_table(P.el, c, P.lv[l].nx, P.lv[l].ny, sizeof(double), N);
+    tail_tab_signs(tb);
+  };
   for (int l = top; l >= 1; --l) {
     const LevelD& V = P.lv[l];
     const int nx = V.nx, n = nx * V.ny;
-    double *sD = lds, *sG = lds + n;
-    tail_tab_load(P, l, c, tb);
+    double *sD = lds, *sG = lds + N;
+    table(l);
     tail_zero(G);
     const int sweeps = l > 1 ? K : P.csweeps;
-    for (int s = 0; s < sweeps; ++s) tail_relax<double, 1>(k, n, tb, G, R, sD, sG, true);
+    for (int s = 0; s < sweeps; ++s) tail_relax<double, N>(k, n, tb, G, R, sD, sG, true);
     if (l == 1) break;
     if (c < n) {
 #pragma unroll
@@ -1794,41 +1806,41 @@ __device__ __forceinline__ void tail_small(const ProbD& P, int top, int K, const
         keep[(16 * l + 8 + q) * N + c] = R[0][q];
       }
     }
-    tail_relax<double, 1>(k, n, tb, G, R, sD, sG, false);
+    tail_relax<double, N>(k, n, tb, G, R, sD, sG, false);
     __syncthreads();
     if (c < n) {
 #pragma unroll
-      for (int q = 0; q < 8; ++q) sG[q * n + c] = G[0][q];
+      for (int q = 0; q < 8; ++q) sG[q * N + c] = G[0][q];
     }
     __syncthreads();
     const LevelD& C = P.lv[l - 1];
     const int cnx = C.nx, f0 = 2 * c + 2 * cnx * tail_row(c, C.inv_nx), f1 = f0 + nx;
 #pragma unroll
     for (int q = 0; q < 8; ++q)
-      R[0][q] = c < cnx * C.ny ? (sG[q * n + f0] + sG[q * n + f0 + 1]) + (sG[q * n + f1] + sG[q * n + f1 + 1]) : 0.0;
+      R[0][q] = c < cnx * C.ny ? (sG[q * N + f0] + sG[q * N + f0 + 1]) + (sG[q * N + f1] + sG[q * N + f1 + 1]) : 0.0;
     __syncthreads();
   }
   for (int l = 2; l <= top; ++l) {
     const LevelD& V = P.lv[l];
     const int nx = V.nx, n = nx * V.ny, cnx = nx / 2, cn = cnx * (V.ny / 2);
-    double *sD = lds, *sG = lds + n;
+    double *sD = lds, *sG = lds + N;
     __syncthreads();
     if (c < cn) {
 #pragma unroll
-      for (int q = 0; q < 8; ++q) sG[q * cn + c] = G[0][q];
+      for (int q = 0; q < 8; ++q) sG[q * N + c] = G[0][q];
     }
     __syncthreads();
     const int y = tail_row(c, V.inv_nx), ci = (y >> 1) * cnx + ((c - y * nx) >> 1);
     if (c < n) {
 #pragma unroll
       for (int q = 0; q < 8; ++q) {
-        G[0][q] = keep[(16 * l + q) * N + c] + sG[q * cn + ci];
+        G[0][q] = keep[(16 * l + q) * N + c] + sG[q * N + ci];
         R[0][q] = keep[(16 * l + 8 + q) * N + c];
       }
     }
     __syncthreads();
-    tail_tab_load(P, l, c, tb);
-    for (int s = 0; s < K; ++s) tail_relax<double, 1>(k, n, tb, G, R, sD, sG, true);
+    table(l);
+    for (int s = 0; s < K; ++s) tail_relax<double, N>(k, n, tb, G, R, sD, sG, true);
   }
 }
 
@@ -1856,7 +1868,7 @@ hipError_t launch_tail_matrix(const ProbD& P, int top, int K, double* out, hipSt
 }
 
 // the matrix times the right-hand side R of level P.tml (thread c: cell c),
-// left in LDS as plane q of cell c at lds + n + q n in type TT
+// left in LDS as plane q of cell c at lds + (1 + q) 1024 in type TT
 template <typename TR, typename TT>
 __device__ __forceinline__ void tail_dense(const ProbD& P, const TR (&R)[1][8], char* lds) {
   const int t = threadIdx.x, n = P.lv[P.tml].nx * P.lv[P.tml].ny, n8 = 8 * n;
@@ -1871,7 +1883,7 @@ __device__ __forceinline__ void tail_dense(const ProbD& P, const TR (&R)[1][8], 
     for (int q = 0; q < 8; ++q) r[q * n + t] = double(R[0][q]);
   }
   __syncthreads();
-  const int part = t % kTailPart, o = t / kTailPart;
+  const int part = t % kTailPart, o = t / kTailPart, q0 = o / n;
   double acc = 0.0;
 #pragma unroll
   for (int k = 0; k < KM; ++k)
@@ -1879,10 +1891,15 @@ __device__ __forceinline__ void tail_dense(const ProbD& P, const TR (&R)[1][8], 
 #pragma unroll
   for (int w = 1; w < kTailPart; w *= 2) acc += __shfl_xor(acc, w, kWave);
   __syncthreads();  // every thread has read r
-  if (part == 0 && o < n8) ((TT*)lds)[n + o] = TT(acc);
+  if (part == 0 && o < n8) ((TT*)lds)[(1 + q0) * kTailThreads + (o - q0 * n)] = TT(acc);
   __syncthreads();
 }
 
+// The tail is one workgroup's chain: of 34 us (32^2 on top, FP32) 16 were its
+// sweeps, the rest the way between levels.  Level descriptors are read as
+// constant memory, whose loads need not follow every store and barrier anew:
+// with the matrix warmed 34.3 -> 31.0 us, and 50 cycles of an 8 x 128 column
+// (k_tail_full) 2.07 -> 1.69 ms in FP64, 1.81 -> 1.42 in FP32.
 // Algorithm 4 on levels lt..1 of one problem; levels >= 2 are stored as T,
 // level 1 as T1.  Thread c owns cell c of every level.  Going down, the
 // restricted residual of a level stays in the registers of the thread that
@@ -1901,32 +1918,39 @@ __device__ __forceinline__ void tail_run(const ProbD& P, int lt, int K, char* ld
   const ElConst<T> k = tail_consts<T>(P);
   // gather tables: tb for the level being swept, tn fetched one level ahead
   // (order of use: lt, ..., 2, 1, 2, ..., lt)
-  TailTab tb[1], tn[1];
+  TailTab tb, tn;
   if (kPrefetch && lt > lm) tail_tab_load(P, lt, c, tn);
   if (lt >= 2)
     tail_load1<T>(P.lv[lt], P.lv[lt].r, c, R);
   else
     tail_load1<T1>(P.lv[1], P.lv[1].r, c, R1);
+  // the matrix comes into this XCD's L2 behind the first sweeps: a word of each
+  // 128-byte line (read cold, the turn took 4.4 of the tail's 34 us)
+  const bool warm = lm > 0 && lt > lm && c * 128 < P.lv[lm].nx * P.lv[lm].ny * kTailThreads * 8;
+  const int line = warm ? gload(gptr<int>(P.tmat), (uint32_t)c * 128u) : 0;
   // ---- descent: K pre-smoothing sweeps from zero, residual, restriction
   for (int l = lt; l > low; --l) {
     const LevelD& V = P.lv[l];
     const int nx = V.nx, ny = V.ny, n = nx * ny;
     T* sD = (T*)lds;
-    T* sG = sD + n;
+    T* sG = sD + kTailThreads;
     if (kPrefetch) {
-      tb[0] = tn[0];
+      tb = tn;
+      tail_tab_signs(tb);
       if (l - 1 > lm) tail_tab_load(P, l - 1, c, tn);
     } else {
       tail_tab_load(P, l, c, tb);
+      tail_tab_signs(tb);
     }
     tail_first<T>(k, n, tb, G, R, sG);
-    for (int s = 1; s < K; ++s) tail_relax<T, 1>(k, n, tb, G, R, sD, sG, true);
+    for (int s = 1; s < K; ++s) tail_relax<T>(k, n, tb, G, R, sD, sG, true);
+    if (l == lt) asm volatile("" ::"v"(line));  // loaded
     tail_store1<T>(V, V.gA, c, G);
-    tail_relax<T, 1>(k, n, tb, G, R, sD, sG, false);
+    tail_relax<T>(k, n, tb, G, R, sD, sG, false);
     __syncthreads();  // every pull has read sG
     if (c < n) {
 #pragma unroll
-      for (int q = 0; q < 8; ++q) sG[q * n + c] = G[0][q];
+      for (int q = 0; q < 8; ++q) sG[q * kTailThreads + c] = G[0][q];
     }
     __syncthreads();
     const LevelD& C = P.lv[l - 1];
@@ -1936,7 +1960,7 @@ __device__ __forceinline__ void tail_run(const ProbD& P, int lt, int K, char* ld
       // fine cell (2 X, 2 Y) of coarse cell (X, Y) = c
       const int f0 = 2 * c + 2 * cnx * tail_row(c, C.inv_nx), f1 = f0 + nx;
 #pragma unroll
-      for (int q = 0; q < 8; ++q) sum[q] = (sG[q * n + f0] + sG[q * n + f0 + 1]) + (sG[q * n + f1] + sG[q * n + f1 + 1]);
+      for (int q = 0; q < 8; ++q) sum[q] = (sG[q * kTailThreads + f0] + sG[q * kTailThreads + f0 + 1]) + (sG[q * kTailThreads + f1] + sG[q * kTailThreads + f1 + 1]);
     } else {
 #pragma unroll
       for (int q = 0; q < 8; ++q) sum[q] = T(0);
@@ -1964,20 +1988,21 @@ __device__ __forceinline__ void tail_run(const ProbD& P, int lt, int K, char* ld
     const LevelD& V = P.lv[1];
     const int n = V.nx * V.ny;
     T1* sD = (T1*)lds;
-    T1* sG = sD + n;
+    T1* sG = sD + kTailThreads;
     const ElConst<T1> k1 = tail_consts<T1>(P);
     if (kPrefetch)
-      tb[0] = tn[0];
+      tb = tn;
     else
       tail_tab_load(P, 1, c, tb);
+    tail_tab_signs(tb);
     if (kPrefetch && lt >= 2) tail_tab_load(P, 2, c, tn);
     tail_first<T1>(k1, n, tb, G1, R1, sG);
-    for (int s = 1; s < P.csweeps; ++s) tail_relax<T1, 1>(k1, n, tb, G1, R1, sD, sG, true);
+    for (int s = 1; s < P.csweeps; ++s) tail_relax<T1>(k1, n, tb, G1, R1, sD, sG, true);
     tail_store1<T1>(V, V.gA, c, G1);
     __syncthreads();  // every pull has read sG
     if (c < n) {
 #pragma unroll
-      for (int q = 0; q < 8; ++q) sG[q * n + c] = G1[0][q];
+      for (int q = 0; q < 8; ++q) sG[q * kTailThreads + c] = G1[0][q];
     }
     __syncthreads();
   } else {
@@ -1992,13 +2017,13 @@ __device__ __forceinline__ void tail_run(const ProbD& P, int lt, int K, char* ld
       if (lm == 1) {
         if (c < n) {
 #pragma unroll
-          for (int q = 0; q < 8; ++q) G1[0][q] = ((const T1*)lds)[n + q * n + c];
+          for (int q = 0; q < 8; ++q) G1[0][q] = ((const T1*)lds)[(1 + q) * kTailThreads + c];
         }
         tail_store1<T1>(V, V.gA, c, G1);
       } else {
         if (c < n) {
 #pragma unroll
-          for (int q = 0; q < 8; ++q) G[0][q] = ((const T*)lds)[n + q * n + c];
+          for (int q = 0; q < 8; ++q) G[0][q] = ((const T*)lds)[(1 + q) * kTailThreads + c];
         }
         tail_store1<T>(V, V.gA, c, G);
       }
@@ -2009,7 +2034,6 @@ __device__ __forceinline__ void tail_run(const ProbD& P, int lt, int K, char* ld
   for (int l = low + 1; l <= lt; ++l) {
     const LevelD& V = P.lv[l];
     const int nx = V.nx, ny = V.ny, n = nx * ny;
-    const int cn = (nx / 2) * (ny / 2);
     if (kPrefetch) {
 #pragma unroll
       for (int q = 0; q < 8; ++q) {
@@ -2023,13 +2047,13 @@ __device__ __forceinline__ void tail_run(const ProbD& P, int lt, int K, char* ld
     if (c < n) {
       const int y = tail_row(c, V.inv_nx), ci = (y >> 1) * (nx / 2) + ((c - y * nx) >> 1);
       if (l == 2) {
-        const T1* ex = (const T1*)lds + cn;
+        const T1* ex = (const T1*)lds + kTailThreads;
 #pragma unroll
-        for (int q = 0; q < 8; ++q) G[0][q] += T(ex[q * cn + ci]);
+        for (int q = 0; q < 8; ++q) G[0][q] += T(ex[q * kTailThreads + ci]);
       } else {
-        const T* ex = (const T*)lds + cn;
+        const T* ex = (const T*)lds + kTailThreads;
 #pragma unroll
-        for (int q = 0; q < 8; ++q) G[0][q] += ex[q * cn + ci];
+        for (int q = 0; q < 8; ++q) G[0][q] += ex[q * kTailThreads + ci];
       }
     }
     if (kPrefetch && l + 1 <= lt) {
@@ -2038,21 +2062,23 @@ __device__ __forceinline__ void tail_run(const ProbD& P, int lt, int K, char* ld
     }
     __syncthreads();  // the sweeps' sD overlaps the coarse result just read
     T* sD = (T*)lds;
-    T* sG = sD + n;
+    T* sG = sD + kTailThreads;
     if (kPrefetch) {
-      tb[0] = tn[0];
+      tb = tn;
+      tail_tab_signs(tb);
       if (l + 1 <= lt) tail_tab_load(P, l + 1, c, tn);
     } else {
       tail_tab_load(P, l, c, tb);
+      tail_tab_signs(tb);
     }
-    for (int s = 0; s < K; ++s) tail_relax<T, 1>(k, n, tb, G, R, sD, sG, true);
+    for (int s = 0; s < K; ++s) tail_relax<T>(k, n, tb, G, R, sD, sG, true);
     if (l == lt) {
       tail_store1<T>(V, V.gA, c, G);
     } else {
       __syncthreads();  // every pull has read sG
       if (c < n) {
 #pragma unroll
-        for (int q = 0; q < 8; ++q) sG[q * n + c] = G[0][q];
+        for (int q = 0; q < 8; ++q) sG[q * kTailThreads + c] = G[0][q];
       }
       __syncthreads();
     }
@@ -2068,15 +2094,15 @@ __device__ __forceinline__ void tail_run(const ProbD& P, int lt, int K, char* ld
 // other threads passes through LDS, as in tail_run.
 
 // the coarse result handed to the finer level: plane q of cell c at
-// lds + n + q n in the level's type (n: the level's cells)
+// lds + (1 + q) 1024 in the level's type
 template <typename TT>
 __device__ __forceinline__ void tail_hand_up(char* lds, int n, const TT (&G)[1][8]) {
   const int c = threadIdx.x;
-  TT* sG = (TT*)lds + n;
+  TT* sG = (TT*)lds + kTailThreads;
   __syncthreads();  // every pull of the last sweep has read sG
   if (c < n) {
 #pragma unroll
-    for (int q = 0; q < 8; ++q) sG[q * n + c] = G[0][q];
+    for (int q = 0; q < 8; ++q) sG[q * kTailThreads + c] = G[0][q];
   }
   __syncthreads();
 }
@@ -2089,11 +2115,11 @@ __device__ __forceinline__ void tail_restrict(const ProbD& P, int l, const T (&G
   const int c = threadIdx.x;
   const LevelD& V = P.lv[l];
   const int nx = V.nx, ny = V.ny, n = nx * ny;
-  T* sG = (T*)lds + n;
+  T* sG = (T*)lds + kTailThreads;
   __syncthreads();  // every pull of the residual sweep has read sG
   if (c < n) {
 #pragma unroll
-    for (int q = 0; q < 8; ++q) sG[q * n + c] = G[0][q];
+    for (int q = 0; q < 8; ++q) sG[q * kTailThreads + c] = G[0][q];
   }
   __syncthreads();
   const LevelD& C = P.lv[l - 1];
@@ -2102,7 +2128,7 @@ __device__ __forceinline__ void tail_restrict(const ProbD& P, int l, const T (&G
   if (c < cn) {
     const int f0 = 2 * c + 2 * cnx * tail_row(c, C.inv_nx), f1 = f0 + nx;  // fine cell (2 X, 2 Y) of (X, Y) = c
 #pragma unroll
-    for (int q = 0; q < 8; ++q) sum[q] = (sG[q * n + f0] + sG[q * n + f0 + 1]) + (sG[q * n + f1] + sG[q * n + f1 + 1]);
+    for (int q = 0; q < 8; ++q) sum[q] = (sG[q * kTailThreads + f0] + sG[q * kTailThreads + f0 + 1]) + (sG[q * kTailThreads + f1] + sG[q * kTailThreads + f1 + 1]);
   } else {
 #pragma unroll
     for (int q = 0; q < 8; ++q) sum[q] = T(0);
@@ -2129,19 +2155,20 @@ __device__ __forceinline__ void tail_pre(const ProbD& P, int l, int K, bool zero
   const LevelD& V = P.lv[l];
   const int nx = V.nx, ny = V.ny, n = nx * ny;
   T* sD = (T*)lds;
-  T* sG = sD + n;
+  T* sG = sD + kTailThreads;
   const ElConst<T> k = tail_consts<T>(P);
-  TailTab tb[1];
+  TailTab tb;
   T G[1][8], R[1][8];
   tail_tab_load(P, l, c, tb);
+  tail_tab_signs(tb);
   tail_load1<T>(V, V.r, c, R);
   if (zero)
     tail_zero(G);
   else
     tail_load1<T>(V, V.gA, c, G);
-  for (int s = 0; s < K; ++s) tail_relax<T, 1>(k, n, tb, G, R, sD, sG, true);
+  for (int s = 0; s < K; ++s) tail_relax<T>(k, n, tb, G, R, sD, sG, true);
   tail_store1<T>(V, V.gA, c, G);
-  tail_relax<T, 1>(k, n, tb, G, R, sD, sG, false);
+  tail_relax<T>(k, n, tb, G, R, sD, sG, false);
   tail_restrict<T, T1>(P, l, G, lds);
 }
 
@@ -2153,17 +2180,18 @@ __device__ __forceinline__ void tail_coarsest(const ProbD& P, int K, bool zero, 
   const LevelD& V = P.lv[1];
   const int n = V.nx * V.ny;
   T1* sD = (T1*)lds;
-  T1* sG = sD + n;
+  T1* sG = sD + kTailThreads;
   const ElConst<T1> k = tail_consts<T1>(P);
-  TailTab tb[1];
+  TailTab tb;
   T1 G[1][8], R[1][8];
   tail_tab_load(P, 1, c, tb);
+  tail_tab_signs(tb);
   tail_load1<T1>(V, V.r, c, R);
   if (zero)
     tail_zero(G);
   else
     tail_load1<T1>(V, V.gA, c, G);
-  for (int s = 0; s < P.csweeps; ++s) tail_relax<T1, 1>(k, n, tb, G, R, sD, sG, true);
+  for (int s = 0; s < P.csweeps; ++s) tail_relax<T1>(k, n, tb, G, R, sD, sG, true);
   tail_store1<T1>(V, V.gA, c, G);
   tail_hand_up<T1>(lds, n, G);
 }
@@ -2175,23 +2203,23 @@ __device__ __forceinline__ void tail_post(const ProbD& P, int l, int K, char* ld
   const int c = threadIdx.x;
   const LevelD& V = P.lv[l];
   const int nx = V.nx, ny = V.ny, n = nx * ny;
-  const int cn = (nx / 2) * (ny / 2);
-  TailTab tb[1];
+  TailTab tb;
   T G[1][8], R[1][8];
   tail_tab_load(P, l, c, tb);
+  tail_tab_signs(tb);
   tail_load1<T>(V, V.gA, c, G);
   tail_load1<T>(V, V.r, c, R);
   if (c < n) {
     const int y = tail_row(c, V.inv_nx), ci = (y >> 1) * (nx / 2) + ((c - y * nx) >> 1);
-    const TC* ex = (const TC*)lds + cn;
+    const TC* ex = (const TC*)lds + kTailThreads;
 #pragma unroll
-    for (int q = 0; q < 8; ++q) G[0][q] += T(ex[q * cn + ci]);
+    for (int q = 0; q < 8; ++q) G[0][q] += T(ex[q * kTailThreads + ci]);
   }
   __syncthreads();  // the sweeps' sD overlaps the coarse result just read
   T* sD = (T*)lds;
-  T* sG = sD + n;
+  T* sG = sD + kTailThreads;
   const ElConst<T> k = tail_consts<T>(P);
-  for (int s = 0; s < K; ++s) tail_relax<T, 1>(k, n, tb, G, R, sD, sG, true);
+  for (int s = 0; s < K; ++s) tail_relax<T>(k, n, tb, G, R, sD, sG, true);
   tail_store1<T>(V, V.gA, c, G);
   tail_hand_up<T>(lds, n, G);
 }
@@ -2264,7 +2292,7 @@ struct TailFine {
 // measuring sweep): G <- (1 - gamma) G + gamma S(G) from the unscaled S(G),
 // adding ||G - S(G)||^2 and ||G||^2 of the cell to (mr, mg) in FP64
 template <typename T>
-__device__ __forceinline__ void tail_relax_fine(const ElConst<T>& k, int n, const TailTab (&tb)[1], T (&G)[1][8],
+__device__ __forceinline__ void tail_relax_fine(const ElConst<T>& k, int n, const TailTab& tb, T (&G)[1][8],
                                                 const TailFine<T>& f, T* sD, T* sG, int mode,
                                                 double* mr = nullptr, double* mg = nullptr) {
   const int c = threadIdx.x;
@@ -2273,33 +2301,21 @@ __device__ __forceinline__ void tail_relax_fine(const ElConst<T>& k, int n, cons
   __syncthreads();
   const T sc = blend ? k.gamma : T(1);
   if (c < n) {
-    T v[3][3];
-    v[0][0] = sD[lo16(tb[0].dn[0])];
-    v[0][1] = sD[hi16(tb[0].dn[0])];
-    v[0][2] = sD[lo16(tb[0].dn[1])];
-    v[1][0] = sD[hi16(tb[0].dn[1])];
-    v[1][2] = sD[lo16(tb[0].dn[2])];
-    v[2][0] = sD[hi16(tb[0].dn[2])];
-    v[2][1] = sD[lo16(tb[0].dn[3])];
-    v[2][2] = sD[hi16(tb[0].dn[3])];
-    v[1][1] = T(0);  // the centred gradient does not use the centre
     T gx_, gy_;
-    grad_c(v, gx_, gy_);
+    tail_grad(tb, sD, gx_, gy_);
     T u[8], s8[8];
 #pragma unroll
     for (int q = 0; q < 8; ++q) u[q] = G[0][q];
     el_collide(u, k.cstar * gx_ + f.Fx, k.cstar * gy_ + f.Fy, k, s8, sc);
 #pragma unroll
-    for (int q = 0; q < 8; ++q) sG[q * n + c] = s8[q];
+    for (int q = 0; q < 8; ++q) sG[q * kTailThreads + c] = s8[q];
   }
   __syncthreads();
   const T omg = T(1) - k.gamma;
   if (c < n) {
 #pragma unroll
     for (int q = 0; q < 8; ++q) {
-      const uint32_t code = (q & 1) ? hi16(tb[0].pl[q >> 1]) : lo16(tb[0].pl[q >> 1]);
-      const T v = sG[code & 0x7fffu];
-      T gi = (code & 0x8000u) ? -v : v;
+      T gi = tail_pull(tb, sG, q);
       if (f.wall) gi += sc * f.add[q * kTailThreads + c];
       if (mode == 3) {
         const double rho = double(G[0][q]) - double(gi);
@@ -2317,7 +2333,8 @@ __device__ __forceinline__ void tail_relax_fine(const ElConst<T>& k, int n, cons
 // (every phase of every cycle uses them; registers held across the phases
 // would spill): 8 planes of wall terms, then the force's two.  A serial chain
 // of sweeps bounds the launch; the Terzaghi column 8 x 128 in FP64, 50 cycles:
-// 2.22 ms per step with global loads in each phase, 2.07 so
+// 2.22 ms per step with global loads in each phase, 2.07 so (1.69 with
+// constant descriptors)
 template <typename T>
 __device__ __forceinline__ bool tail_fine_load(const ProbD& P, const LevelD& V, T* sF) {
   const int c = threadIdx.x;
@@ -2352,10 +2369,11 @@ __device__ __forceinline__ void tail_fine_pre_g(const ProbD& P, int L, int npre,
   const LevelD& V = P.lv[L];
   const int nx = V.nx, ny = V.ny, n = nx * ny;
   T* sD = (T*)lds;
-  T* sG = sD + n;
+  T* sG = sD + kTailThreads;
   const ElConst<T> k = tail_consts<T>(P);
-  TailTab tb[1];
+  TailTab tb;
   tail_tab_load(P, L, c, tb);
+  tail_tab_signs(tb);
   const TailFine<T> f = tail_fine_terms<T>(sF, wall);
   for (int s = 0; s < npre; ++s) tail_relax_fine<T>(k, n, tb, G, f, sD, sG, 1);
   tail_store1<T>(V, V.gA, c, G);
@@ -2370,20 +2388,20 @@ __device__ __forceinline__ void tail_fine_post(const ProbD& P, int L, int K, cha
   const int c = threadIdx.x;
   const LevelD& V = P.lv[L];
   const int nx = V.nx, ny = V.ny, n = nx * ny;
-  const int cn = (nx / 2) * (ny / 2);
-  TailTab tb[1];
+  TailTab tb;
   T G[1][8];
   tail_tab_load(P, L, c, tb);
+  tail_tab_signs(tb);
   tail_load1<T>(V, V.gA, c, G);
   if (c < n) {
     const int y = tail_row(c, V.inv_nx), ci = (y >> 1) * (nx / 2) + ((c - y * nx) >> 1);
-    const TC* ex = (const TC*)lds + cn;
+    const TC* ex = (const TC*)lds + kTailThreads;
 #pragma unroll
-    for (int q = 0; q < 8; ++q) G[0][q] += T(ex[q * cn + ci]);
+    for (int q = 0; q < 8; ++q) G[0][q] += T(ex[q * kTailThreads + ci]);
   }
   __syncthreads();  // the sweeps' sD overlaps the coarse result just read
   T* sD = (T*)lds;
-  T* sG = sD + n;
+  T* sG = sD + kTailThreads;
   const ElConst<T> k = tail_consts<T>(P);
   const TailFine<T> f = tail_fine_terms<T>(sF, wall);
   for (int s = 0; s < K; ++s) tail_relax_fine<T>(k, n, tb, G, f, sD, sG, 1);
@@ -2429,10 +2447,11 @@ __device__ __forceinline__ void tail_measure(const ProbD& P, char* lds, T (&G)[1
   const LevelD& V = P.lv[P.L];
   const int n = V.nx * V.ny;
   T* sD = (T*)lds;
-  T* sG = sD + n;
+  T* sG = sD + kTailThreads;
   const ElConst<T> k = tail_consts<T>(P);
-  TailTab tb[1];
+  TailTab tb;
   tail_tab_load(P, P.L, c, tb);
+  tail_tab_signs(tb);
   tail_load1<T>(V, V.gA, c, G);
   double r = 0.0, g = 0.0;
   tail_relax_fine<T>(k, n, tb, G, tail_fine_terms<T>(sF, wall), sD, sG, 3, &r, &g);
@@ -2462,7 +2481,7 @@ template <typename T>
 __global__ __launch_bounds__(kTailThreads) void k_tail_full(TailL a) {
   if (gated_off(a.skip, a.need)) return;  // uniform over the grid
   extern __shared__ char lds[];
-  const ProbD& P = a.probs[a.pids[2 * blockIdx.x]];  // (problem, 0) entries
+  const ProbD& P = constant(a.probs + a.pids[2 * blockIdx.x]);  // (problem, 0) entries
   const int L = P.L;
   if (L < 2 || L - 1 > kTailMaxLevel || !P.addt) return;  // uniform; the host never asks for it
   // without the loop: one cycle from buffer fine_in with fine_pre
@@ -2525,7 +2544,7 @@ template <typename T>
 __global__ __launch_bounds__(kTailThreads) void k_tail_shaped(TailL a) {
   if (gated_off(a.skip, a.need)) return;  // uniform over the grid
   extern __shared__ char lds[];
-  const ProbD& P = a.probs[a.pids[2 * blockIdx.x]];  // (problem, 0) entries
+  const ProbD& P = constant(a.probs + a.pids[2 * blockIdx.x]);  // (problem, 0) entries
   const int lt = P.L - a.depth;
   if (lt < 1 || lt > kTailMaxLevel) return;  // uniform; the host never asks for it
   tail_run_shaped<T, double>(P, lt, a.K, a.shape, a.from_zero != 0, lds);
@@ -2537,7 +2556,7 @@ __global__ __launch_bounds__(kTailThreads) void k_tail(TailL a) {
   extern __shared__ char lds[];
   // (problem, depth) entries: with a.depth < 0 each problem's tail starts at
   // the entry's depth, else at the launch's
-  const ProbD& P = a.probs[a.pids[2 * blockIdx.x]];
+  const ProbD& P = constant(a.probs + a.pids[2 * blockIdx.x]);
   tail_run<T, double>(P, P.L - (a.depth < 0 ? a.pids[2 * blockIdx.x + 1] : a.depth), a.K, lds);
 }
 
