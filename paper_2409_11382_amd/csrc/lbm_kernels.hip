@@ -1637,6 +1637,17 @@ __device__ __forceinline__ ElConst<T> tail_consts(const ProbD& P) {
   return k;
 }
 
+// a level of one wave needs no barrier between its own LDS writes and reads
+// (in FP32: 64^2 tail 30.3 -> 29.1 us; in FP64 it gained nothing)
+template <typename T> __device__ __forceinline__ void tail_sync(int n) {
+  if (sizeof(T) == 8 || __builtin_expect(n > kWave, 1)) {  // uniform
+    __syncthreads();
+  } else {
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
+  }
+}
+
 // one application of S on a whole level held by the workgroup: thread c owns
 // cell c; G (iterate) and R (right-hand side) in registers, gathers through the
 // level's tables.  blend: G <- (1 - gamma) G + gamma S(G); otherwise
@@ -1649,7 +1660,7 @@ __device__ __forceinline__ void tail_relax(const ElConst<T>& k, int n, const Tai
                                            const T (&R)[1][8], T* sD, T* sG, bool blend) {
   const int c = threadIdx.x;
   if (c < n) sD[c] = k.kD * el_ms(G[0]);
-  __syncthreads();
+  tail_sync<T>(n);
   if (c < n) {
     T gx_, gy_;
     tail_grad(tb, sD, gx_, gy_);
@@ -1661,7 +1672,7 @@ __device__ __forceinline__ void tail_relax(const ElConst<T>& k, int n, const Tai
 #pragma unroll
     for (int q = 0; q < 8; ++q) sG[q * PS + c] = s8[q];
   }
-  __syncthreads();
+  tail_sync<T>(n);
   const T omg = T(1) - k.gamma;
   if (c < n) {
 #pragma unroll
@@ -1686,7 +1697,7 @@ __device__ __forceinline__ void tail_first(const ElConst<T>& k, int n, const Tai
 #pragma unroll
     for (int q = 0; q < 8; ++q) sG[q * kTailThreads + c] = s8[q];
   }
-  __syncthreads();
+  tail_sync<T>(n);
   if (c < n) {
 #pragma unroll
     for (int q = 0; q < 8; ++q) G[0][q] = tail_pull(tb, sG, q);
@@ -1869,14 +1880,17 @@ hipError_t launch_tail_matrix(const ProbD& P, int top, int K, double* out, hipSt
 
 // the matrix times the right-hand side R of level P.tml (thread c: cell c),
 // left in LDS as plane q of cell c at lds + (1 + q) 1024 in type TT
-template <typename TR, typename TT>
-__device__ __forceinline__ void tail_dense(const ProbD& P, const TR (&R)[1][8], char* lds) {
-  const int t = threadIdx.x, n = P.lv[P.tml].nx * P.lv[P.tml].ny, n8 = 8 * n;
+constexpr int kTailM = 8 * kTailDenseCells / kTailPart;  // entries per thread
+__device__ __forceinline__ void tail_dense_load(const ProbD& P, double (&m)[kTailM]) {
+  const int n8 = 8 * P.lv[P.tml].nx * P.lv[P.tml].ny;
   const GPtr<double> M = gptr<double>(P.tmat);
-  constexpr int KM = 8 * kTailDenseCells / kTailPart;
-  double m[KM];
 #pragma unroll
-  for (int k = 0; k < KM; ++k) m[k] = k * kTailPart < n8 ? gload(M + k * kTailThreads, (uint32_t)t * 8u) : 0.0;
+  for (int k = 0; k < kTailM; ++k)
+    m[k] = k * kTailPart < n8 ? gload(M + k * kTailThreads, (uint32_t)threadIdx.x * 8u) : 0.0;
+}
+template <typename TR, typename TT>
+__device__ __forceinline__ void tail_dense(const ProbD& P, const TR (&R)[1][8], const double (&m)[kTailM], char* lds) {
+  const int t = threadIdx.x, n = P.lv[P.tml].nx * P.lv[P.tml].ny, n8 = 8 * n;
   double* r = (double*)lds;
   if (t < n) {
 #pragma unroll
@@ -1886,7 +1900,7 @@ __device__ __forceinline__ void tail_dense(const ProbD& P, const TR (&R)[1][8], 
   const int part = t % kTailPart, o = t / kTailPart, q0 = o / n;
   double acc = 0.0;
 #pragma unroll
-  for (int k = 0; k < KM; ++k)
+  for (int k = 0; k < kTailM; ++k)
     if (k * kTailPart < n8) acc += m[k] * r[k * kTailPart + part];
 #pragma unroll
   for (int w = 1; w < kTailPart; w *= 2) acc += __shfl_xor(acc, w, kWave);
@@ -1924,9 +1938,12 @@ __device__ __forceinline__ void tail_run(const ProbD& P, int lt, int K, char* ld
     tail_load1<T>(P.lv[lt], P.lv[lt].r, c, R);
   else
     tail_load1<T1>(P.lv[1], P.lv[1].r, c, R1);
-  // the matrix comes into this XCD's L2 behind the first sweeps: a word of each
-  // 128-byte line (read cold, the turn took 4.4 of the tail's 34 us)
-  const bool warm = lm > 0 && lt > lm && c * 128 < P.lv[lm].nx * P.lv[lm].ny * kTailThreads * 8;
+  // the matrix (read cold at the turn, it took 4.4 of the tail's 34 us): in FP32
+  // fetched before the sweeps of the level above, in FP64, which lacks the
+  // registers, brought into this XCD's L2 behind the first sweeps, a word of
+  // each 128-byte line
+  double m[kTailM];
+  const bool warm = !kPrefetch && lm > 0 && lt > lm && c * 128 < P.lv[lm].nx * P.lv[lm].ny * kTailThreads * 8;
   const int line = warm ? gload(gptr<int>(P.tmat), (uint32_t)c * 128u) : 0;
   // ---- descent: K pre-smoothing sweeps from zero, residual, restriction
   for (int l = lt; l > low; --l) {
@@ -1942,9 +1959,10 @@ __device__ __forceinline__ void tail_run(const ProbD& P, int lt, int K, char* ld
       tail_tab_load(P, l, c, tb);
       tail_tab_signs(tb);
     }
+    if (kPrefetch && lm > 0 && l == low + 1) tail_dense_load(P, m);
     tail_first<T>(k, n, tb, G, R, sG);
     for (int s = 1; s < K; ++s) tail_relax<T>(k, n, tb, G, R, sD, sG, true);
-    if (l == lt) asm volatile("" ::"v"(line));  // loaded
+    if (!kPrefetch && l == lt) asm volatile("" ::"v"(line));  // loaded
     tail_store1<T>(V, V.gA, c, G);
     tail_relax<T>(k, n, tb, G, R, sD, sG, false);
     __syncthreads();  // every pull has read sG
@@ -1976,10 +1994,11 @@ __device__ __forceinline__ void tail_run(const ProbD& P, int lt, int K, char* ld
     }
     __syncthreads();  // sG is reused by the next level
   }
-  // prefetch the next level's stored iterate and right-hand side for the way
-  // up (in FP64 the registers are not there: those levels load when they start)
+  // prefetch the next level's stored iterate and right-hand side for the way up
+  // (in FP64 later levels' registers are not there during the sweeps: their
+  // loads follow the sweeps of the level below)
   T Gn[1][8], Rn[1][8];
-  if (kPrefetch && lt > low) {
+  if (lt > low) {
     tail_load1<T>(P.lv[low + 1], P.lv[low + 1].gA, c, Gn);
     tail_load1<T>(P.lv[low + 1], P.lv[low + 1].r, c, Rn);
   }
@@ -2007,10 +2026,11 @@ __device__ __forceinline__ void tail_run(const ProbD& P, int lt, int K, char* ld
     __syncthreads();
   } else {
     if (kPrefetch && lt > lm) tail_tab_load(P, lm + 1, c, tn);
+    if (!kPrefetch || lt == lm) tail_dense_load(P, m);
     if (lm == 1)
-      tail_dense<T1, T1>(P, R1, lds);
+      tail_dense<T1, T1>(P, R1, m, lds);
     else
-      tail_dense<T, T>(P, R, lds);
+      tail_dense<T, T>(P, R, m, lds);
     if (lt == lm) {  // the matrix is the whole tail
       const LevelD& V = P.lv[lm];
       const int n = V.nx * V.ny;
@@ -2034,15 +2054,10 @@ __device__ __forceinline__ void tail_run(const ProbD& P, int lt, int K, char* ld
   for (int l = low + 1; l <= lt; ++l) {
     const LevelD& V = P.lv[l];
     const int nx = V.nx, ny = V.ny, n = nx * ny;
-    if (kPrefetch) {
 #pragma unroll
-      for (int q = 0; q < 8; ++q) {
-        G[0][q] = Gn[0][q];
-        R[0][q] = Rn[0][q];
-      }
-    } else {
-      tail_load1<T>(V, V.gA, c, G);
-      tail_load1<T>(V, V.r, c, R);
+    for (int q = 0; q < 8; ++q) {
+      G[0][q] = Gn[0][q];
+      R[0][q] = Rn[0][q];
     }
     if (c < n) {
       const int y = tail_row(c, V.inv_nx), ci = (y >> 1) * (nx / 2) + ((c - y * nx) >> 1);
@@ -2075,6 +2090,10 @@ __device__ __forceinline__ void tail_run(const ProbD& P, int lt, int K, char* ld
     if (l == lt) {
       tail_store1<T>(V, V.gA, c, G);
     } else {
+      if (!kPrefetch) {
+        tail_load1<T>(P.lv[l + 1], P.lv[l + 1].gA, c, Gn);
+        tail_load1<T>(P.lv[l + 1], P.lv[l + 1].r, c, Rn);
+      }
       __syncthreads();  // every pull has read sG
       if (c < n) {
 #pragma unroll
