@@ -877,6 +877,7 @@ void region_rules(const Engine& E, int d, int64_t cells, DepthLists& r) {
 bp_status engine_upload(Engine& E) {
   const size_t np = E.probs.size();
   if (np > E.probs_cap) return fail(BP_ERR_WORKSPACE, "too many problems for the engine area");
+  if (np >> kTileLevelShift) return fail(BP_ERR_ARG, "too many problems");  // 2^26
   std::vector<ProbD> pd(np);
   for (size_t i = 0; i < np; ++i) pd[i] = E.probs[i]->d;
   E.maxL = 1;
@@ -917,11 +918,14 @@ bp_status engine_upload(Engine& E) {
           const int A = set_apps(set);
           const int nt = set >= kSetFused ? sweepn_tiles(v.nx, v.ny, v.dbl, A, E.shift && d == 0, alt_at(E, d, A))
                                           : sweep_tiles(v.nx, v.ny);
-          // multi-application launches take the tile's column and row packed
+          // multi-application launches take the level with the problem, and
+          // the tile's column and row packed
           const LevelD& D = pd[i].lv[l];
           for (int t = 0; t < nt; ++t)
-            tiles.push_back(make_int2(
-                (int)i, set >= kSetFused ? (t / D.tiles_xn[A] << D.tile_shift[A] | t % D.tiles_xn[A]) : t));
+            tiles.push_back(set >= kSetFused
+                                ? make_int2((int)i | l << kTileLevelShift,
+                                            t / D.tiles_xn[A] << D.tile_shift[A] | t % D.tiles_xn[A])
+                                : make_int2((int)i, t));
         }
         if (E.xcd_order) xcd_order(tiles, E.depth[d].off[set][g]);
         E.depth[d].cnt[set][g] = (int)tiles.size() - E.depth[d].off[set][g];

@@ -16,6 +16,7 @@
 namespace biot {
 
 constexpr int kMaxLevels = 16;
+constexpr int kTileLevelShift = 26;     // multi-application tiles: problem | level << 26
 constexpr int kTileY = 12;              // output rows of a sweep tile (even: 2x2 restriction pairs)
 // flow tile: 8 waves of 2 rows, one halo row and column on each side
 constexpr int kFlowWaves = 8, kFlowRows = 2;
