@@ -235,7 +235,7 @@ void make_layout(const bp_problem* p, Layout& lo) {
   lo.ntiles_fine2 = 0;
   for (int A = 2; A <= 5; ++A)
     for (int alt = 0; alt < 2; ++alt)
-      lo.ntiles_fine2 = std::max(lo.ntiles_fine2, sweepn_tiles(p->nx, p->ny, lo.fdbl, A, lo.shift, alt && A != 4));
+      lo.ntiles_fine2 = std::max(lo.ntiles_fine2, sweepn_tiles(p->nx, p->ny, lo.fdbl, A, lo.shift, alt));
   lo.off_part2 = take((size_t)lo.ntiles_fine2 * 2 * 8);
   lo.off_scal = take(128);
   if (lo.lag)
@@ -283,7 +283,7 @@ size_t tile_entries_for(const Layout& lo) {
     const bool sh = lo.shift && l == lo.L;
     for (int A = 2; A <= 5; ++A)  // either region
       t += (size_t)std::max(sweepn_tiles(lo.lv[l].nx, lo.lv[l].ny, lo.lv[l].dbl, A, sh, false),
-                            sweepn_tiles(lo.lv[l].nx, lo.lv[l].ny, lo.lv[l].dbl, A, sh, A != 4));
+                            sweepn_tiles(lo.lv[l].nx, lo.lv[l].ny, lo.lv[l].dbl, A, sh, true));
   }
   t += (size_t)sweep_tiles(lo.nx, lo.ny);
   t += (size_t)cell_blocks(lo.nx, lo.ny) * 2;
@@ -703,6 +703,7 @@ struct DepthLists {
   bool quad = false;  // four applications per launch
   bool fres = false;  // restriction fused into the last pre-smoothing launch
   bool qwide = false; // its four-application form on 64-column regions
+  bool qlow = false;  // four applications on regions of 24 rows
   bool tall = false;  // pairs on tall regions
   bool rtall = false; // pairs with the restriction on tall regions
   int tail_off = 0, tail_cnt = 0;  // problems whose coarse tail starts here
@@ -811,7 +812,7 @@ void xcd_order(std::vector<int2>& tiles, size_t off) {
 bool quad_at(const Engine& E, int d) { return E.depth[d].quad && !(d == 0 && E.fdbl && E.shift); }
 // the alternative region for A applications per launch at depth d
 bool alt_at(const Engine& E, int d, int A) {
-  return A == 2 ? E.depth[d].tall : (A == 3 ? E.depth[d].rtall : (A == 5 && E.depth[d].qwide));
+  return A == 2 ? E.depth[d].tall : (A == 3 ? E.depth[d].rtall : (A == 4 ? E.depth[d].qlow : E.depth[d].qwide));
 }
 
 // blocks of a depth's launches of A applications
@@ -833,6 +834,8 @@ int64_t depth_blocks(const Engine& E, int d, int A, bool alt) {
 //   blocks, and 256 with the restriction) against two pairs.  320^2: 17.1 for
 //   four, 23.2 for two pairs, with the restriction 17.6 against 27.6; 368^2,
 //   in a third and second round: 21.6 and 23.2, 27.9 and 27.8.
+// - four applications on regions of 24 rows while one round holds them (a 160^2
+//   step 228.4 us, on 32 rows 236.6; 128^2 in FP64 246.5 and 258).
 // - four with the restriction: narrow regions in one round (184 x 120 cells
 //   in 160 blocks: a 736 x 480 step 555, on wide ones 566), wide beyond (224^2
 //   in 361 narrow blocks: an 896^2 step 786, wide 778).
@@ -857,6 +860,7 @@ void region_rules(const Engine& E, int d, int64_t cells, DepthLists& r) {
   r.quad = cells <= E.quad_max_cells;
   if (E.quad_max_cells == kQuadMaxCells) r.quad = r.quad || (rounds(4, false, 2) <= 1 && rounds(5, true, 1) <= 1);
   r.quad = r.quad && E.quad;
+  r.qlow = rounds(4, true, 1) <= 1;
   r.qwide = cells > E.qnarrow_max_cells;
   if (E.qnarrow_max_cells == kQuadNarrowResCells) r.qwide = r.qwide && rounds(5, false, 1) > 1;
   r.tall = r.rtall = cells <= E.tall_max_cells;
@@ -1250,7 +1254,7 @@ template <typename T, typename Tc>
 hipError_t sweep_launch(const Op& o, hipStream_t s) {
   switch (o.apps) {
     case 5: return o.alt ? sweepn_launch<T, Tc, 4, true, true>(o, s) : sweepn_launch<T, Tc, 4, true, false>(o, s);
-    case 4: return sweepn_launch<T, Tc, 4, false, false>(o, s);
+    case 4: return o.alt ? sweepn_launch<T, Tc, 4, false, true>(o, s) : sweepn_launch<T, Tc, 4, false, false>(o, s);
     case 3: return o.alt ? sweepn_launch<T, Tc, 2, true, true>(o, s) : sweepn_launch<T, Tc, 2, true, false>(o, s);
     case 2: return o.alt ? sweepn_launch<T, Tc, 2, false, true>(o, s) : sweepn_launch<T, Tc, 2, false, false>(o, s);
     default: break;
@@ -2119,7 +2123,8 @@ std::string op_name(const Op& o) {
 // by the process until it ends.  In host code `scratch` names a host-side
 // stand-in, never a device address: the device address comes from
 // hipGetSymbolAddress, once per device with that device current.
-constexpr size_t kScratchBytes = (size_t(64) << 20) + tail_matrix_bytes(kTailDenseCells);  // 64 MiB, and a coarse matrix
+// 64 MiB, a coarse matrix and the tile lists of low regions
+constexpr size_t kScratchBytes = (size_t(64) << 20) + tail_matrix_bytes(kTailDenseCells) + (128 << 10);
 static __device__ __align__(256) char scratch[kScratchBytes];
 constexpr int kMaxDevices = 64;
 std::mutex g_scratch_mu;

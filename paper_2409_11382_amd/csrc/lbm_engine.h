@@ -210,13 +210,16 @@ hipError_t launch_tsweep(const SweepL& a, int ntiles, hipStream_t s);
 // - four applications are used only on depths of few cells, where the launch
 //   is bound by the dependent work of one block: a 32 x 32 region (16 x 16
 //   outputs) spreads such a depth over about four times as many compute units
-//   as a 64-column one.  With the restriction (A = 5, halo 10) the narrow
+//   as a 64-column one.  ALT (12 waves, 32 x 24 region, 16 x 8 outputs) serves
+//   depths that it puts on at most 256 blocks: an application is then the
+//   issue of three waves per SIMD instead of four (64^2: 11.2 us, 12.2 on 16
+//   waves; FP64 12.3 and 14.2).  With the restriction (A = 5, halo 10) the narrow
 //   region keeps only 12 x 12 outputs; ALT (64 x 32 region, 44 x 12 outputs)
 //   serves the larger of those depths.
 template <typename T, bool SHIFT, int A, bool ALT>
 __host__ __device__ constexpr int sweepn_waves() {
   if (A == 3 && sizeof(T) == 8 && !SHIFT) return ALT ? 12 : 16;
-  return A >= 4 ? 16 : ((!ALT || (sizeof(T) == 8 && SHIFT)) ? 8 : (A == 2 ? 16 : 12));
+  return A >= 4 ? (A == 4 && ALT ? 12 : 16) : ((!ALT || (sizeof(T) == 8 && SHIFT)) ? 8 : (A == 2 ? 16 : 12));
 }
 template <typename T, bool SHIFT, int A, bool ALT>
 __host__ __device__ constexpr int sweepn_rows() {
@@ -226,12 +229,12 @@ __host__ __device__ constexpr int sweepn_rows() {
                                                       : (A == 3 ? 3 : ((ALT && !(sizeof(T) == 8 && SHIFT)) ? 2 : (sizeof(T) == 8 ? 2 : 3))));
 }
 template <int A, bool ALT>
-__host__ __device__ constexpr int sweepn_cols() { return (A <= 3 || ALT) ? kWave : 32; }
+__host__ __device__ constexpr int sweepn_cols() { return (A <= 3 || (A == 5 && ALT)) ? kWave : 32; }
 template <typename T, bool SHIFT, int A, bool ALT>
 __host__ __device__ constexpr int sweepn_region_rows() {
   return sweepn_waves<T, SHIFT, A, ALT>() * sweepn_rows<T, SHIFT, A, ALT>() * (kWave / sweepn_cols<A, ALT>());
 }
-inline int sweepn_tile_x(int A, bool alt) { return ((A <= 3 || alt) ? kWave : 32) - 4 * A; }
+inline int sweepn_tile_x(int A, bool alt) { return ((A <= 3 || (A == 5 && alt)) ? kWave : 32) - 4 * A; }
 template <int A, bool ALT>
 inline int sweepn_region_rows_rt(bool dbl, bool shift) {
   return dbl ? (shift ? sweepn_region_rows<double, true, A, ALT>() : sweepn_region_rows<double, false, A, ALT>())
@@ -243,13 +246,12 @@ inline int sweepn_tile_y(int A, bool dbl, bool shift, bool alt) {
   switch (A) {
     case 2: rr = alt ? sweepn_region_rows_rt<2, true>(dbl, shift) : sweepn_region_rows_rt<2, false>(dbl, shift); break;
     case 3: rr = alt ? sweepn_region_rows_rt<3, true>(dbl, shift) : sweepn_region_rows_rt<3, false>(dbl, shift); break;
-    case 4: rr = sweepn_region_rows_rt<4, false>(dbl, shift); break;
+    case 4: rr = alt ? sweepn_region_rows_rt<4, true>(dbl, shift) : sweepn_region_rows_rt<4, false>(dbl, shift); break;
     default: rr = alt ? sweepn_region_rows_rt<5, true>(dbl, shift) : sweepn_region_rows_rt<5, false>(dbl, shift); break;
   }
   return rr - 4 * A;
 }
-// ALT: the alternative region of the applications per launch (not for four
-// applications without the restriction); ref64: shifted FP32 storage where
+// ALT: the alternative region of the applications per launch; ref64: shifted FP32 storage where
 // some problem of the launch keeps FP64 references (selects the kernel variant
 // that reads either precision, per problem)
 template <typename T, typename Tc, bool FINE, bool SHIFT, int APPS, bool RES, bool ALT = false>

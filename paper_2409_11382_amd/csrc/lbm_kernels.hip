@@ -364,7 +364,6 @@ template <typename T, typename Tc, bool FINE, bool SHIFT, int APPS, bool RES, bo
 __global__ __launch_bounds__((kWave * sweepn_waves<T, SHIFT, APPS + RES, ALT>())) void k_tsweep2(SweepL a) {
   if (gated_off(a.skip, a.need)) return;  // uniform over the grid
   constexpr int A = APPS + (RES ? 1 : 0);
-  static_assert(!ALT || A != 4, "four applications without the restriction have one region");
   constexpr int NW = sweepn_waves<T, SHIFT, A, ALT>();
   constexpr int NK = sweepn_rows<T, SHIFT, A, ALT>();
   constexpr int H = 2 * A;         // halo
@@ -2690,12 +2689,12 @@ BIOT_SWEEP(double, double)
   template hipError_t launch_tsweep2<T, Tc, false, false, 2, false, ALT>(const SweepL&, int, bool, hipStream_t); \
   template hipError_t launch_tsweep2<T, Tc, false, false, 2, true, ALT>(const SweepL&, int, bool, hipStream_t);  \
   template hipError_t launch_tsweep2<T, Tc, false, false, 4, true, ALT>(const SweepL&, int, bool, hipStream_t);  \
-  template hipError_t launch_tsweep2<T, Tc, true, false, 4, true, ALT>(const SweepL&, int, bool, hipStream_t);
+  template hipError_t launch_tsweep2<T, Tc, true, false, 4, true, ALT>(const SweepL&, int, bool, hipStream_t);  \
+  template hipError_t launch_tsweep2<T, Tc, false, false, 4, false, ALT>(const SweepL&, int, bool, hipStream_t); \
+  template hipError_t launch_tsweep2<T, Tc, true, false, 4, false, ALT>(const SweepL&, int, bool, hipStream_t);
 #define BIOT_SWEEPN(T, Tc)                                                                            \
   BIOT_SWEEPN_ALT(T, Tc, false)                                                                       \
-  BIOT_SWEEPN_ALT(T, Tc, true)                                                                        \
-  template hipError_t launch_tsweep2<T, Tc, false, false, 4, false>(const SweepL&, int, bool, hipStream_t);  \
-  template hipError_t launch_tsweep2<T, Tc, true, false, 4, false>(const SweepL&, int, bool, hipStream_t);
+  BIOT_SWEEPN_ALT(T, Tc, true)
 BIOT_SWEEPN(float, float)
 BIOT_SWEEPN(float, double)
 BIOT_SWEEPN(double, double)
@@ -2705,6 +2704,8 @@ template hipError_t launch_tsweep2<float, float, true, true, 4, false>(const Swe
 template hipError_t launch_tsweep2<float, float, true, true, 4, true>(const SweepL&, int, bool, hipStream_t);
 template hipError_t launch_tsweep2<float, double, true, true, 4, false>(const SweepL&, int, bool, hipStream_t);
 template hipError_t launch_tsweep2<float, double, true, true, 4, true>(const SweepL&, int, bool, hipStream_t);
+template hipError_t launch_tsweep2<float, float, true, true, 4, false, true>(const SweepL&, int, bool, hipStream_t);
+template hipError_t launch_tsweep2<float, double, true, true, 4, false, true>(const SweepL&, int, bool, hipStream_t);
 template hipError_t launch_tsweep2<float, float, true, true, 4, true, true>(const SweepL&, int, bool, hipStream_t);
 template hipError_t launch_tsweep2<float, double, true, true, 4, true, true>(const SweepL&, int, bool, hipStream_t);
 // FP64 shifted storage has no LDS room for four applications; the schedule
@@ -2715,6 +2716,10 @@ hipError_t launch_tsweep2<double, double, true, true, 4, false>(const SweepL&, i
 }
 template <>
 hipError_t launch_tsweep2<double, double, true, true, 4, true>(const SweepL&, int, bool, hipStream_t) {
+  return hipErrorInvalidConfiguration;
+}
+template <>
+hipError_t launch_tsweep2<double, double, true, true, 4, false, true>(const SweepL&, int, bool, hipStream_t) {
   return hipErrorInvalidConfiguration;
 }
 template <>

@@ -101,9 +101,9 @@ def test_smallest_levels_as_a_matrix(lbm, shape, walls, sweeps):
 
 
 @pytest.mark.parametrize("prec,tol", [("fp64", 1e-10), ("fp32_shifted", 1e-5)])
-@pytest.mark.parametrize("nx,ny", [(512, 250), (530, 250), (640, 400)])
+@pytest.mark.parametrize("nx,ny", [(256, 128), (272, 128), (512, 250), (530, 250), (640, 400)])
 def test_regions_chosen_by_their_rounds(lbm, nx, ny, prec, tol):
-    """Sizes at the lines between launch shapes: 512 blocks of four
+    """Sizes at the lines between launch shapes: 256 low and 512 blocks of four
     applications and more, one and two rounds of the pairs' regions; the
     chosen shapes and the pairs' default regions against the oracle."""
     p = _problem("DTSD", nx, ny)
