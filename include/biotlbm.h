@@ -307,7 +307,8 @@ bp_status bp_destroy(bp_solver *s);
 
 /* For callers that cannot allocate (code under HIP graph capture, tight
  * serving loops, harnesses that forbid hipMalloc): bp_create on a workspace
- * the library owns, a file-scope static device array of 64 MiB per device
+ * the library owns, a file-scope static device array of 64 MiB and the coarse
+ * levels' matrix (128 KiB) per device
  * (held from the library's first use on that device until the process ends;
  * a problem whose bp_workspace_bytes exceed it is refused with
  * BP_ERR_WORKSPACE).  The solver then allocates nothing: no device or pinned
