@@ -1423,15 +1423,20 @@ bp_status engine_init(Engine& E, char* area, size_t area_bytes, size_t probs_cap
   return BP_OK;
 }
 
-// a stream under capture refuses what reads or writes host memory: it takes
-// the general copies, which report that
-bool staged(const Engine& E, size_t row_bytes) {
+// is the caller capturing the engine's stream (or can that not be told)?
+bool capturing(const Engine& E) {
   hipStreamCaptureStatus c = hipStreamCaptureStatusNone;
   if (hipStreamIsCapturing(E.stream, &c) != hipSuccess) {
     (void)hipGetLastError();
-    return false;
+    return true;
   }
-  return E.stage.n > 0 && row_bytes <= E.stage.slot && c == hipStreamCaptureStatusNone;
+  return c != hipStreamCaptureStatusNone;
+}
+
+// a stream under capture refuses what reads or writes host memory: it takes
+// the general copies, which report that
+bool staged(const Engine& E, size_t row_bytes) {
+  return E.stage.n > 0 && row_bytes <= E.stage.slot && !capturing(E);
 }
 
 // bytes of a problem's fields
@@ -1485,7 +1490,10 @@ bp_status fixed_step(Engine& E, int* left = nullptr) {
   TraceRange r("coupled step");
   if (!E.graph_valid) BPCHK(build_graph(E));
   int n = 1;
-  if (left && *left >= 4 && E.graph && !E.graph4) {  // batches and servers take one step at a time
+  // the four-step graph is captured when it is first wanted (batches and
+  // servers take one step at a time), which a stream under the caller's
+  // capture refuses: the steps then go in one by one
+  if (left && *left >= 4 && E.graph && !E.graph4 && !capturing(E)) {
     std::vector<Op> four;
     for (int k = 0; k < 4; ++k) four.insert(four.end(), E.step_ops.begin(), E.step_ops.end());
     BPCHK(capture_ops(E, four, &E.graph4));
