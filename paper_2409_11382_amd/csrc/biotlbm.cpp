@@ -839,10 +839,15 @@ int64_t depth_blocks(const Engine& E, int d, int A, bool alt) {
 // - four with the restriction: narrow regions in one round (184 x 120 cells
 //   in 160 blocks: a 736 x 480 step 555, on wide ones 566), wide beyond (224^2
 //   in 361 narrow blocks: an 896^2 step 786, wide 778).
-// - pairs in FP32 shifted storage: a round of tall regions (one block per CU)
-//   takes about 8.6 after the first 5.5, a round of the default (two per CU)
-//   10.7 after 7.  512^2: 14.3 against 17.1; 640^2 21.8, 18.5; 736^2 23.4,
-//   25.0; 1024^2 38.8, 35.7.
+// - pairs in FP32 shifted storage: tall regions (one block per CU) in one
+//   round, or in two where the default (two blocks per CU) takes two as well.
+//   Default and tall: 512^2 16.4 and 14.0 (one round each), 736^2 23.3 and
+//   22.9, 800^2 24.9 and 24.6 (two each); 640^2 17.6 and 21.3 (one against two),
+//   896^2 27.4 and 30.8 (two against three).  Beyond, the default's second block
+//   hides each block's waits and tall loses at every size: 1024^2 33.8 and
+//   39.8, 1216^2 40.3 and 47.1, 1280^2 43.0 and 49.5, 1408^2 49.8 and 57.8,
+//   1536^2 59.1 and 69.8, 1824^2 85.2 and 106.6, 1920^2 96.0 and 118.2, 2048^2
+//   104.7 and 134.5.
 // - pairs in FP32: both regions have the same outputs; one per CU while one
 //   round suffices (512^2 12.8, two per CU 14.4), else two (1024^2 37.4, 32.0).
 // - pairs in FP64: tall where that is one round and the default more than one
@@ -869,7 +874,8 @@ void region_rules(const Engine& E, int d, int64_t cells, DepthLists& r) {
     r.tall = rounds(2, false, 2) > 1 && rounds(2, true, 1) <= 1;
     r.rtall = 8 * rounds(3, false, 1) > 9 * rounds(3, true, 1);
   } else if (shift) {
-    r.tall = 55 + 86 * rounds(2, true, 1) <= 70 + 107 * rounds(2, false, 2);
+    const int64_t t = rounds(2, true, 1);
+    r.tall = t <= 1 || (t == 2 && rounds(2, false, 2) == 2);
     r.rtall = rounds(3, true, 1) <= 1 && rounds(3, false, 1) > 1;
   } else {
     r.tall = rounds(2, true, 1) <= 1;
