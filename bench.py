@@ -221,15 +221,15 @@ def cpu_baseline_others(threads):
 def dominant_kernel(solver, iters, label="float,float,fine,shift", bytes_per_app_cell=80):
     """The finest-level smoothing launch of the step (the fine smoothing sweep
     that carries most of a step's traffic): two applications per launch
-    (k_tsweep2<...,2,no-restriction>), or four where the tuning puts the
+    (k_tsweep2<...,2,no-restriction>), or four where the schedule puts the
     finest depth on four-application launches.  Average device time of
     `iters` back-to-back launches (one captured graph, HIP events on the
     solver's stream) and its algorithmic bytes per launch: per application and
     cell the populations read and written, the explicit force and the
     displacement reference read (8 + 8 + 2 + 2 values of 4 B in FP32 shifted
     storage: 80 B), times the applications of the launch."""
-    apps = 4 if solver.tuning()["quad_max_cells"] >= solver.p.ncells else 2
     us, nbytes = solver.time_kernel(4, iters)
+    apps = round(nbytes / (solver.p.ncells * bytes_per_app_cell))
     achieved = nbytes / (us * 1e-6) / 1e9
     return {"bound": "hbm", "achieved": round(achieved, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
             "frac": round(achieved / HBM_PEAK_GBS, 4), "traffic": None,

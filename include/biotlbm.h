@@ -241,20 +241,21 @@ bp_status bp_stats(const bp_solver *s, bp_run_stats *st);
  *   four applications with the restriction on 32 x 32 regions
  *                                    if cells <= quad_res_narrow_max_cells
  *                                    (else on 64 x 32 regions)
- * A bound at its initial value (256^2, 512^2 and 128^2 cells for quad, tall
- * and narrow) leaves the choice to the blocks the depth's launches would have:
- * the shape whose blocks take the cheaper rounds on the chip.
+ * quad, tall and narrow are initially BP_TUNING_BY_RULE, which leaves the choice
+ * to the blocks the depth's launches would have: the shape whose blocks take
+ * the cheaper rounds on the chip.  Any other value is the bound itself.
  * bp_autotune searches the bounds by coordinate descent: each bound in turn
- * takes the value among five candidates whose time steps run fastest on this
+ * takes the value among a few candidates whose time steps run fastest on this
  * engine (HIP events, `steps` steps per candidate after one warm-up step; a
  * candidate must beat the best so far by 2%), the others held.  It steps the
  * problems while timing and re-initialises them at the end, so it must be
  * called before the first step (else BP_ERR_STATE) and needs a fixed number
  * of V-cycles (ne_fixed > 0, else BP_ERR_ARG).  *out (may be null) receives
  * the chosen bounds and the measured milliseconds per step.  bp_set_tuning
- * applies bounds (>= 0) at any time, for instance ones found earlier for the
- * same sizes; bp_get_tuning reports the current ones (ms_per_step 0).  The
- * server uses the default bounds. */
+ * applies bounds (>= 0, or BP_TUNING_BY_RULE for the three) at any time, for
+ * instance ones found earlier for the same sizes; bp_get_tuning reports the
+ * current ones (ms_per_step 0).  The server uses the initial ones. */
+#define BP_TUNING_BY_RULE INT64_MIN
 typedef struct {
   int64_t quad_max_cells;
   int64_t tall_max_cells;

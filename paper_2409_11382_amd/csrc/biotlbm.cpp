@@ -691,12 +691,12 @@ int set_apps(int set) {
 constexpr int64_t kFuseResCells = int64_t(1) << 40;
 // bounds on the cells a depth covers in all (bp_tuning, and the environment
 // variables BIOT_QUAD_MAX_CELLS and BIOT_TALL_MAX_CELLS) for four applications
-// per launch, the narrow region of four with the restriction, and the tall
-// regions of pairs.  A bound left at its value here yields to the block counts
-// of region_rules() below.
+// per launch, the tall regions of pairs and the narrow region of four with the
+// restriction.  A bound that nobody gave is BP_TUNING_BY_RULE and leaves the
+// choice to region_rules() below, which starts from these cells.
+constexpr int64_t kByRule = BP_TUNING_BY_RULE;
 constexpr int64_t kQuadMaxCells = 256 * 256;
 constexpr int64_t kQuadNarrowResCells = 128 * 128;
-constexpr int64_t kTallMaxCells = 512 * 512;
 struct DepthLists {
   int off[8][3] = {};
   int cnt[8][3] = {};
@@ -771,10 +771,10 @@ struct Engine {
   bool fuse = true;       // the same where every plane fits the launches' 32-bit offsets
   bool quad = true;  // four-application sweeps on small coarse levels
   // launch-shape bounds (cells a depth covers in all); bp_tuning
-  int64_t quad_max_cells = kQuadMaxCells;
-  int64_t tall_max_cells = kTallMaxCells;
+  int64_t quad_max_cells = kByRule;
+  int64_t tall_max_cells = kByRule;
   int64_t fres_max_cells = kFuseResCells;
-  int64_t qnarrow_max_cells = kQuadNarrowResCells;
+  int64_t qnarrow_max_cells = kByRule;
   bool fuse_res = true;  // restriction fused into pre-smoothing on latency-bound depths
   double* host_pin = nullptr;
   bool own_pin = false;        // host_pin from hipHostMalloc (else host_buf)
@@ -862,14 +862,17 @@ void region_rules(const Engine& E, int d, int64_t cells, DepthLists& r) {
     const int64_t slots = 256 * per_cu;
     return (depth_blocks(E, d, A, alt) + slots - 1) / slots;
   };
-  r.quad = cells <= E.quad_max_cells;
-  if (E.quad_max_cells == kQuadMaxCells) r.quad = r.quad || (rounds(4, false, 2) <= 1 && rounds(5, true, 1) <= 1);
+  r.quad = E.quad_max_cells != kByRule
+               ? cells <= E.quad_max_cells
+               : cells <= kQuadMaxCells || (rounds(4, false, 2) <= 1 && rounds(5, true, 1) <= 1);
   r.quad = r.quad && E.quad;
   r.qlow = rounds(4, true, 1) <= 1;
-  r.qwide = cells > E.qnarrow_max_cells;
-  if (E.qnarrow_max_cells == kQuadNarrowResCells) r.qwide = r.qwide && rounds(5, false, 1) > 1;
-  r.tall = r.rtall = cells <= E.tall_max_cells;
-  if (E.tall_max_cells != kTallMaxCells) return;
+  r.qwide = E.qnarrow_max_cells != kByRule ? cells > E.qnarrow_max_cells
+                                           : cells > kQuadNarrowResCells && rounds(5, false, 1) > 1;
+  if (E.tall_max_cells != kByRule) {
+    r.tall = r.rtall = cells <= E.tall_max_cells;
+    return;
+  }
   if (E.fdbl) {
     r.tall = rounds(2, false, 2) > 1 && rounds(2, true, 1) <= 1;
     r.rtall = 8 * rounds(3, false, 1) > 9 * rounds(3, true, 1);
@@ -1785,9 +1788,10 @@ void tuning_of(const Engine& E, bp_tuning* t) {
 
 bp_status apply_tuning(Engine& E, const bp_tuning* t) {
   if (!t) return fail(BP_ERR_ARG, "null tuning");
-  if (t->quad_max_cells < 0 || t->tall_max_cells < 0 || t->fuse_res_max_cells < 0 ||
-      t->quad_res_narrow_max_cells < 0)
-    return fail(BP_ERR_ARG, "tuning bounds must be >= 0");
+  auto ok = [](int64_t v) { return v >= 0 || v == kByRule; };
+  if (!ok(t->quad_max_cells) || !ok(t->tall_max_cells) || t->fuse_res_max_cells < 0 ||
+      !ok(t->quad_res_narrow_max_cells))
+    return fail(BP_ERR_ARG, "tuning bounds must be >= 0 (or BP_TUNING_BY_RULE)");
   HIPCHK(hipStreamSynchronize(E.stream));
   E.quad_max_cells = t->quad_max_cells;
   E.tall_max_cells = t->tall_max_cells;
@@ -1839,25 +1843,25 @@ bp_status autotune(Engine& E, int steps, bp_tuning* out) {
     if (P->step != 0) return fail(BP_ERR_STATE, "autotune runs before the first step");
   if (steps < 1) steps = 1;
   int64_t* knob[4] = {&E.quad_max_cells, &E.tall_max_cells, &E.fres_max_cells, &E.qnarrow_max_cells};
-  static const int64_t cand[4][5] = {{0, 64 * 64, 128 * 128, 256 * 256, 512 * 512},
-                                     {0, 256 * 256, 512 * 512, 1024 * 1024, 2048 * 2048},
-                                     {0, 256 * 256, 512 * 512, 2048 * 2048, int64_t(1) << 40},
-                                     {0, 64 * 64, 128 * 128, 256 * 256, 512 * 512}};
+  static const std::vector<int64_t> cand[4] = {{kByRule, 0, 64 * 64, 128 * 128, 256 * 256, 512 * 512},
+                                               {kByRule, 0, 256 * 256, 512 * 512, 1024 * 1024, 2048 * 2048},
+                                               {0, 256 * 256, 512 * 512, 2048 * 2048, kFuseResCells},
+                                               {kByRule, 0, 64 * 64, 128 * 128, 256 * 256, 512 * 512}};
   BPCHK(engine_upload(E));
   double best = 0.0;
   BPCHK(time_steps_median(E, steps, &best));
   for (int k = 0; k < 4; ++k) {
     const int64_t keep = *knob[k];
     int64_t bestv = keep;
-    for (int c = 0; c < 5; ++c) {
-      if (cand[k][c] == keep) continue;
-      *knob[k] = cand[k][c];
+    for (const int64_t v : cand[k]) {
+      if (v == keep) continue;
+      *knob[k] = v;
       BPCHK(engine_upload(E));
       double ms = 0.0;
       BPCHK(time_steps_median(E, steps, &ms));
       if (ms < 0.98 * best) {
         best = ms;
-        bestv = cand[k][c];
+        bestv = v;
       }
     }
     *knob[k] = bestv;

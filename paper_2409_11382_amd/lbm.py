@@ -44,6 +44,10 @@ class _Problem(C.Structure):
                 ("lag", C.c_int32)]
 
 
+# a launch-shape bound that nobody gave: the schedule chooses (biotlbm.h)
+TUNING_BY_RULE = -(1 << 63)
+
+
 class _Tuning(C.Structure):
     _fields_ = [("quad_max_cells", C.c_int64), ("tall_max_cells", C.c_int64),
                 ("fuse_res_max_cells", C.c_int64), ("quad_res_narrow_max_cells", C.c_int64),

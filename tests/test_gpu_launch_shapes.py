@@ -1,5 +1,5 @@
-"""GPU test of the launch shapes that the schedule picks where no bound is
-given: the profile names the region of each launch."""
+"""GPU tests of the launch shapes that the schedule picks, where no bound is
+given and where one is: the profile names the region of each launch."""
 import pytest
 
 from paper_2409_11382_amd import problem as P
@@ -33,3 +33,31 @@ def test_tall_pairs_where_they_are_faster(lbm, n, tall):
     s.close()
     assert ("pair alt shift f32" in names) == tall, names
     assert ("pair shift f32" in names) != tall, names
+
+
+@pytest.mark.parametrize("n,bound,cells,shape", [(736, "tall_max_cells", 512 * 512, "pair alt"),
+                                                 (320, "quad_max_cells", 256 * 256, "quad")])
+def test_every_given_bound_is_literal(lbm, n, bound, cells, shape):
+    """A bound below the finest level's cells keeps it from the launch that the
+    rule takes there, whatever the bound's value; the reported bounds applied
+    to another solver give the same launches, by rule or by bound."""
+    p = P.loaded_strip(n=n, ne_fixed=2)
+    s = lbm.Solver(p, "fp32_shifted")
+    assert s.tuning()[bound] == lbm.TUNING_BY_RULE
+    by_rule = _finest(s)
+    assert any(shape in k for k in by_rule)
+    t = lbm.Solver(p, "fp32_shifted")
+    t.set_tuning(s.tuning())
+    assert _finest(t) == by_rule
+    s.set_tuning({bound: cells})
+    assert s.tuning()[bound] == cells
+    assert not any(shape in k for k in _finest(s))
+    t.set_tuning(s.tuning())
+    assert _finest(t) == _finest(s)
+    s.set_tuning({bound: lbm.TUNING_BY_RULE})
+    assert _finest(s) == by_rule
+    for bad in (-1, lbm.TUNING_BY_RULE + 1):
+        with pytest.raises(lbm.BiotError):
+            s.set_tuning({bound: bad})
+    s.close()
+    t.close()
