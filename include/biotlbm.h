@@ -244,6 +244,8 @@ bp_status bp_stats(const bp_solver *s, bp_run_stats *st);
  * quad, tall and narrow are initially BP_TUNING_BY_RULE, which leaves the choice
  * to the blocks the depth's launches would have: the shape whose blocks take
  * the cheaper rounds on the chip.  Any other value is the bound itself.
+ * A finest level whose planes take 4 GiB and more runs pairs in their default
+ * region whatever the bounds.
  * bp_autotune searches the bounds by coordinate descent: each bound in turn
  * takes the value among a few candidates whose time steps run fastest on this
  * engine (HIP events, `steps` steps per candidate after one warm-up step; a

@@ -662,6 +662,7 @@ struct Op {
   TailL tl{};
   int count = 0;          // tiles / problems
   bool alt = false;       // multi-application launch: the alternative region
+  bool wide = false;      // multi-application launch: planes beyond 32-bit offsets
   int set = 0;            // sweeps: the tile-list set (engine_upload)
   int group = 0;          // sweeps: the storage group of the tile list
 };
@@ -767,8 +768,9 @@ struct Engine {
   // deepest point of the cycle when the tails start at several depths
   bool merge_tails = true;
   int tail_all_off = 0, tail_all_cnt = 0, tail_depths = 0;
-  bool want_fuse = true;  // several applications per launch in the time-step schedule
-  bool fuse = true;       // the same where every plane fits the launches' 32-bit offsets
+  bool fuse = true;       // several applications per launch in the time-step schedule
+  bool wide = false;      // some finest level's plane lies beyond 32-bit byte offsets
+  int64_t off32_bytes = int64_t(1) << 32;  // planes of at least this many bytes lie beyond
   bool quad = true;  // four-application sweeps on small coarse levels
   // launch-shape bounds (cells a depth covers in all); bp_tuning
   int64_t quad_max_cells = kByRule;
@@ -858,6 +860,7 @@ int64_t depth_blocks(const Engine& E, int d, int A, bool alt) {
 //   640^2 35.8, 39.1; 736^2 48.1, 43.0).
 void region_rules(const Engine& E, int d, int64_t cells, DepthLists& r) {
   const bool shift = E.shift && d == 0;
+  if (E.wide && d == 0) return;  // pairs in the default region
   auto rounds = [&](int A, bool alt, int per_cu) {
     const int64_t slots = 256 * per_cu;
     return (depth_blocks(E, d, A, alt) + slots - 1) / slots;
@@ -895,13 +898,15 @@ bp_status engine_upload(Engine& E) {
   for (size_t i = 0; i < np; ++i) pd[i] = E.probs[i]->d;
   E.maxL = 1;
   E.ref64 = false;
-  E.fuse = E.want_fuse;
+  E.wide = false;
   for (auto* P : E.probs) {
     E.maxL = std::max(E.maxL, P->L);
     E.ref64 = E.ref64 || (P->lo.shift && P->lo.ref64);
     // the multi-application launches address a plane by 32-bit byte offsets
+    // where each fits; a coarser level's always does (a quarter of the cells in
+    // at most 8 bytes: 4 GiB there belong to 2^31 cells, a workspace of 500 GB)
     const int64_t size = (P->lo.fdbl || (P->lo.shift && P->lo.ref64)) ? 8 : 4;
-    if (P->lo.plane * size >= int64_t(1) << 32) E.fuse = false;
+    E.wide = E.wide || P->lo.plane * size >= E.off32_bytes;
   }
   std::vector<int2> tiles;
   E.depth.assign(E.maxL, DepthLists());
@@ -1015,6 +1020,7 @@ void add_sweeps(Engine& E, std::vector<Op>& ops, int d, int set, int mode, int i
     o.kind = OP_SWEEP;
     o.apps = set_apps(set);
     o.alt = alt_at(E, d, o.apps);
+    o.wide = E.wide && d == 0;
     o.mode = mode;
     o.tdbl = g == 2;
     o.cdbl = g >= 1;
@@ -1255,6 +1261,13 @@ void build_step_ops(Engine& E, std::vector<Op>& ops) {
 template <typename T, typename Tc, int APPS, bool RES, bool ALT>
 hipError_t sweepn_launch(const Op& o, hipStream_t s) {
   if (o.sw.depth != 0) return launch_tsweep2<T, Tc, false, false, APPS, RES, ALT>(o.sw, o.count, s);
+  if (o.wide) {
+    if constexpr (APPS == 2 && !ALT)
+      return o.shift ? launch_tsweep2_wide<T, Tc, true, RES>(o.sw, o.count, s)
+                     : launch_tsweep2_wide<T, Tc, false, RES>(o.sw, o.count, s);
+    else
+      return hipErrorInvalidConfiguration;  // region_rules() asks for none
+  }
   return o.shift ? launch_tsweep2<T, Tc, true, true, APPS, RES, ALT>(o.sw, o.count, o.ref64, s)
                  : launch_tsweep2<T, Tc, true, false, APPS, RES, ALT>(o.sw, o.count, s);
 }
@@ -1412,7 +1425,8 @@ bp_status engine_init(Engine& E, char* area, size_t area_bytes, size_t probs_cap
   if (const char* e = std::getenv("BIOT_NO_GRAPH")) E.use_graph = (std::atoi(e) == 0);
   if (const char* e = std::getenv("BIOT_NO_XCD_ORDER")) E.xcd_order = (std::atoi(e) == 0);
   if (const char* e = std::getenv("BIOT_NO_MERGE_TAIL")) E.merge_tails = (std::atoi(e) == 0);
-  if (const char* e = std::getenv("BIOT_NO_FUSE")) E.want_fuse = (std::atoi(e) == 0);
+  if (const char* e = std::getenv("BIOT_NO_FUSE")) E.fuse = (std::atoi(e) == 0);
+  if (const char* e = std::getenv("BIOT_OFFSET32_BYTES")) E.off32_bytes = std::min(E.off32_bytes, (int64_t)std::atoll(e));
   if (const char* e = std::getenv("BIOT_NO_QUAD")) E.quad = (std::atoi(e) == 0);
   if (const char* e = std::getenv("BIOT_QUAD_MAX_CELLS")) E.quad_max_cells = std::atoll(e);
   if (const char* e = std::getenv("BIOT_TALL_MAX_CELLS")) E.tall_max_cells = std::atoll(e);
@@ -2427,7 +2441,7 @@ bp_status create_solver(const bp_problem* p, const Layout& lo, char* w, void* hi
   if (rc == BP_OK && !no_alloc) stage_init(s->E.stage, field_bytes(*p));
   s->E.csweeps = p->coarse_sweeps;
   s->E.lag = p->lag != 0;
-  if (s->E.lag) s->E.want_fuse = false;  // the lag runs single applications
+  if (s->E.lag) s->E.fuse = false;  // the lag runs single applications
   if (rc == BP_OK) rc = setup_problem(p, lo, w, st, s->P);
   if (rc == BP_OK) {
     s->E.probs = {&s->P};

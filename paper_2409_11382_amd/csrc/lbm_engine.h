@@ -260,6 +260,11 @@ template <typename T, typename Tc, bool FINE, bool SHIFT, int APPS, bool RES, bo
 inline hipError_t launch_tsweep2(const SweepL& a, int ntiles, hipStream_t s) {
   return launch_tsweep2<T, Tc, FINE, SHIFT, APPS, RES, ALT>(a, ntiles, false, s);
 }
+// pairs on the finest level in the default region for planes of 4 GiB and more;
+// references in either precision, per problem.  Single applications took 382 ms
+// for a step of two cycles on 32768 x 16384 cells in FP32 shifted, pairs 204
+template <typename T, typename Tc, bool SHIFT, bool RES>
+hipError_t launch_tsweep2_wide(const SweepL& a, int ntiles, hipStream_t s);
 template <typename T, bool SHIFT>
 hipError_t launch_tflow(const CellL& a, int ntiles, hipStream_t s);
 template <typename T>

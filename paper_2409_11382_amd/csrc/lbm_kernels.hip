@@ -360,7 +360,12 @@ hipError_t launch_tsweep(const SweepL& a, int ntiles, hipStream_t s) {
 // R64: shifted storage whose references may be FP64 (FP64 populations, or a
 // problem above the size where FP32 references lose accuracy); without it the
 // reference arithmetic is FP32 only.
-template <typename T, typename Tc, bool FINE, bool SHIFT, int APPS, bool RES, bool ALT, bool R64>
+// WIDE: planes of 4 GiB and more (finest level only), whose cells lie beyond a
+// 32-bit byte offset: a wave's row, which is one row there, joins the scalar
+// base, and the lane's offset lies within it.  32768 x 16384 cells in FP32
+// shifted: 13.6 ms a pair; 21.0 with 64-bit offsets per lane, whose registers
+// leave one block on a CU.
+template <typename T, typename Tc, bool FINE, bool SHIFT, int APPS, bool RES, bool ALT, bool R64, bool WIDE = false>
 __global__ __launch_bounds__((kWave * sweepn_waves<T, SHIFT, APPS + RES, ALT>())) void k_tsweep2(SweepL a) {
   if (gated_off(a.skip, a.need)) return;  // uniform over the grid
   constexpr int A = APPS + (RES ? 1 : 0);
@@ -386,6 +391,7 @@ __global__ __launch_bounds__((kWave * sweepn_waves<T, SHIFT, APPS + RES, ALT>())
   __shared__ BcT sBy[2][3][FINE ? RX : 1];
   __shared__ BcT sBx[2][3][FINE ? RR : 1];
   constexpr int PS = (RR - 2) * RX;  // plane stride of sS
+  static_assert(!WIDE || (FINE && S == 1), "a wave holds one row of the finest level");
 
   const int2 te = a.tiles[blockIdx.x];
   // the entry names the level too: one dependent descriptor load less (steps of
@@ -437,12 +443,20 @@ __global__ __launch_bounds__((kWave * sweepn_waves<T, SHIFT, APPS + RES, ALT>())
   // to LDS and the coarse correction would make each row wait for its own):
   // 1024^2 pairs 35.7 -> 33.4 us, 2048^2 108.7 -> 104.8
   uint32_t off[NK], coff[NK];  // byte offset of the row's cell in a plane, of its coarse cell in a coarse plane
+  int64_t row[WIDE ? NK : 1];  // WIDE: the row's first cell, and off counts from there
+  auto at = [&](auto base, int kk) {
+    if constexpr (WIDE)
+      return base + row[kk];
+    else
+      return base;
+  };
 #pragma unroll
   for (int kk = 0; kk < NK; ++kk) {
     const int j = (w + NW * kk) * S + sub;
     const int y = y0 - H + j;
     const int gy = pery ? wrap_index(y, ny, RR) : clampi(y, 0, ny - 1);
-    off[kk] = ((uint32_t)gy * (uint32_t)pitch + (uint32_t)gx) * (uint32_t)sizeof(T);
+    if constexpr (WIDE) row[kk] = (int64_t)__builtin_amdgcn_readfirstlane(gy) * pitch;
+    off[kk] = ((WIDE ? 0u : (uint32_t)gy * (uint32_t)pitch) + (uint32_t)gx) * (uint32_t)sizeof(T);
     coff[kk] = ((uint32_t)(gy >> 1) * (uint32_t)cpitch + (uint32_t)(gx >> 1)) * (uint32_t)sizeof(Tc);
   }
   double e64[R64 ? NK : 1][2];
@@ -455,7 +469,7 @@ __global__ __launch_bounds__((kWave * sweepn_waves<T, SHIFT, APPS + RES, ALT>())
     for (int q = 0; q < 8; ++q)
 #pragma unroll
       for (int kk = 0; kk < NK; ++kk) {
-        G[kk][q] = zero_in ? T(0) : gload(gin + q * plane, off[kk]);
+        G[kk][q] = zero_in ? T(0) : gload(at(gin + q * plane, kk), off[kk]);
         if (!FINE) Rv[FINE ? 0 : kk][q] = gload(gptr<T>(V.r) + q * plane, off[kk]);
       }
   }
@@ -466,13 +480,13 @@ __global__ __launch_bounds__((kWave * sweepn_waves<T, SHIFT, APPS + RES, ALT>())
       for (int q = 0; q < 8; ++q) G[kk][q] = T(0);
       if (!zero_in) {
 #pragma unroll
-        for (int q = 0; q < 8; ++q) G[kk][q] = gload(gin + q * plane, off[kk]);
+        for (int q = 0; q < 8; ++q) G[kk][q] = gload(at(gin + q * plane, kk), off[kk]);
       }
     }
     if (FINE) {
       const GPtr<T> Ft = gptr<T>(P.Ft);
-      Fx[FINE ? kk : 0] = gload(Ft, off[kk]);
-      Fy[FINE ? kk : 0] = gload(Ft + plane, off[kk]);
+      Fx[FINE ? kk : 0] = gload(at(Ft, kk), off[kk]);
+      Fy[FINE ? kk : 0] = gload(at(Ft + plane, kk), off[kk]);
     } else if (ROWS) {
       const GPtr<T> rr = gptr<T>(V.r);
 #pragma unroll
@@ -481,12 +495,12 @@ __global__ __launch_bounds__((kWave * sweepn_waves<T, SHIFT, APPS + RES, ALT>())
     const uint32_t cell = off[kk] / (uint32_t)sizeof(T);
     if (R64 && r64) {
       const GPtr<double> e = gptr<double>(eref);
-      e64[R64 ? kk : 0][0] = gload(e, cell * 8u);
-      e64[R64 ? kk : 0][1] = gload(e + plane, cell * 8u);
+      e64[R64 ? kk : 0][0] = gload(at(e, kk), cell * 8u);
+      e64[R64 ? kk : 0][1] = gload(at(e + plane, kk), cell * 8u);
     } else if (SHIFT) {
       const GPtr<float> e = gptr<float>(eref);
-      e32[SHIFT ? kk : 0][0] = gload(e, cell * 4u);
-      e32[SHIFT ? kk : 0][1] = gload(e + plane, cell * 4u);
+      e32[SHIFT ? kk : 0][0] = gload(at(e, kk), cell * 4u);
+      e32[SHIFT ? kk : 0][1] = gload(at(e + plane, kk), cell * 4u);
     }
   }
   if (pro) {
@@ -769,7 +783,7 @@ __global__ __launch_bounds__((kWave * sweepn_waves<T, SHIFT, APPS + RES, ALT>())
         for (int q = 0; q < 8; ++q) G[kk][q] = omg * G[kk][q] + gi[q];
         if (out) {
 #pragma unroll
-          for (int q = 0; q < 8; ++q) gstore(gout + q * plane, off[kk], G[kk][q]);
+          for (int q = 0; q < 8; ++q) gstore(at(gout + q * plane, kk), off[kk], G[kk][q]);
         }
       } else if (!RES && app == A - 1) {
         if (a.partials == 1 && out) {
@@ -798,15 +812,15 @@ __global__ __launch_bounds__((kWave * sweepn_waves<T, SHIFT, APPS + RES, ALT>())
             const double ex = own_x(), ey = own_y();
             const uint32_t cell = off[kk] / (uint32_t)sizeof(T);
             if (r64) {
-              gstore(gptr<double>(eo), cell * 8u, ex + double(m10));
-              gstore(gptr<double>(eo) + plane, cell * 8u, ey + double(m01));
+              gstore(at(gptr<double>(eo), kk), cell * 8u, ex + double(m10));
+              gstore(at(gptr<double>(eo) + plane, kk), cell * 8u, ey + double(m01));
             } else {
-              gstore(gptr<float>(eo), cell * 4u, float(ex) + float(m10));
-              gstore(gptr<float>(eo) + plane, cell * 4u, float(ey) + float(m01));
+              gstore(at(gptr<float>(eo), kk), cell * 4u, float(ex) + float(m10));
+              gstore(at(gptr<float>(eo) + plane, kk), cell * 4u, float(ey) + float(m01));
             }
           }
 #pragma unroll
-          for (int q = 0; q < 8; ++q) gstore(gout + q * plane, off[kk], gn[q]);
+          for (int q = 0; q < 8; ++q) gstore(at(gout + q * plane, kk), off[kk], gn[q]);
         }
       } else {
 #pragma unroll
@@ -873,6 +887,14 @@ hipError_t launch_tsweep2(const SweepL& a, int ntiles, bool ref64, hipStream_t s
   } else {
     hipLaunchKernelGGL((k_tsweep2<T, Tc, FINE, SHIFT, APPS, RES, ALT, SHIFT && dbl>), dim3(ntiles), block, 0, s, a);
   }
+  return hipGetLastError();
+}
+
+template <typename T, typename Tc, bool SHIFT, bool RES>
+hipError_t launch_tsweep2_wide(const SweepL& a, int ntiles, hipStream_t s) {
+  if (ntiles <= 0) return hipSuccess;
+  const dim3 block(kWave * sweepn_waves<T, SHIFT, 2 + (RES ? 1 : 0), false>());
+  hipLaunchKernelGGL((k_tsweep2<T, Tc, true, SHIFT, 2, RES, false, SHIFT, true>), dim3(ntiles), block, 0, s, a);
   return hipGetLastError();
 }
 
@@ -2700,6 +2722,15 @@ BIOT_SWEEPN(float, double)
 BIOT_SWEEPN(double, double)
 #undef BIOT_SWEEPN
 #undef BIOT_SWEEPN_ALT
+#define BIOT_SWEEPN_WIDE(T, Tc)                                                            \
+  template hipError_t launch_tsweep2_wide<T, Tc, false, false>(const SweepL&, int, hipStream_t); \
+  template hipError_t launch_tsweep2_wide<T, Tc, false, true>(const SweepL&, int, hipStream_t);  \
+  template hipError_t launch_tsweep2_wide<T, Tc, true, false>(const SweepL&, int, hipStream_t);  \
+  template hipError_t launch_tsweep2_wide<T, Tc, true, true>(const SweepL&, int, hipStream_t);
+BIOT_SWEEPN_WIDE(float, float)
+BIOT_SWEEPN_WIDE(float, double)
+BIOT_SWEEPN_WIDE(double, double)
+#undef BIOT_SWEEPN_WIDE
 template hipError_t launch_tsweep2<float, float, true, true, 4, false>(const SweepL&, int, bool, hipStream_t);
 template hipError_t launch_tsweep2<float, float, true, true, 4, true>(const SweepL&, int, bool, hipStream_t);
 template hipError_t launch_tsweep2<float, double, true, true, 4, false>(const SweepL&, int, bool, hipStream_t);
