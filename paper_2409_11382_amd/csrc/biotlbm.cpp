@@ -2085,15 +2085,21 @@ double op_bytes(const Engine& E, const Op& o) {
       return b;
     }
     case OP_TAIL: {
-      // the levels of the tail, each application's populations and rhs once
+      // the levels of the tail, each application's populations and rhs once;
+      // those that are one matrix (V-visits from zero): the matrix
       double b = 0.0;
       for (const Prob* P : E.probs) {
         const int td = o.tl.depth < 0 ? P->lo.tail_depth : o.tl.depth;
         if (td <= 0 || P->lo.tail_depth != td) continue;
-        for (int l = 1; l <= P->L - td; ++l) {
+        const int tml = (o.tl.shape == 0 && o.tl.from_zero) ? P->lo.tml : 0;
+        for (int l = tml + 1; l <= P->L - td; ++l) {
           const double n = (double)P->lo.lv[l].nx * P->lo.lv[l].ny, ls = P->lo.lv[l].dbl ? 8.0 : 4.0;
           const int apps = l == 1 ? P->d.csweeps : 2 * E.K + 1;
           b += n * apps * 24.0 * ls;
+        }
+        if (tml > 0) {
+          const double n8 = 8.0 * P->lo.lv[tml].nx * P->lo.lv[tml].ny;
+          b += n8 * n8 * 8.0;
         }
       }
       return b;

@@ -61,3 +61,23 @@ def test_every_given_bound_is_literal(lbm, n, bound, cells, shape):
             s.set_tuning({bound: bad})
     s.close()
     t.close()
+
+
+@pytest.mark.parametrize("cycle", [P.CYCLE_V, P.CYCLE_W])
+@pytest.mark.parametrize("prec,size", [("fp32_shifted", 4), ("fp64", 8)])
+def test_bytes_of_the_coarse_tail(lbm, prec, size, cycle):
+    """The profile charges a tail the sweeps it runs (2K + 1 a level, populations
+    in and out and the right-hand side, the coarsest level in FP64 with its own
+    number) and, in a V-cycle, the matrix in place of its levels of at most 16
+    cells: 64^2, tail of 32^2 and below."""
+    K = 3
+    s = lbm.Solver(P.loaded_strip(n=64, K=K, ne_fixed=2).replace(cycle=cycle), prec)
+    row = [r for r in s.profile_step(1) if r["name"].startswith("tail")][0]
+    s.close()
+    sweep = lambda n, apps, v: n * n * apps * 24 * v
+    want = sum(sweep(n, 2 * K + 1, size) for n in (32, 16, 8))
+    if cycle == P.CYCLE_V:
+        want += (8 * 16) ** 2 * 8
+    else:
+        want += sweep(4, 2 * K + 1, size) + sweep(2, 2 * K, 8)
+    assert row["bytes_per_step"] == row["launches"] * want
