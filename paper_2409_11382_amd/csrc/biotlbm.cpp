@@ -720,6 +720,7 @@ struct Stage {
   static constexpr size_t kSlot = 512 << 10;
   static constexpr int kSlots = 8;
   char* mem = nullptr;
+  size_t want = 0;  // bytes of the fields it is to serve (0: none)
   size_t slot = 0;  // bytes of a slot, before it a header of kHead bytes
   int n = 0;        // slots (0: none, the caller copies)
   hipEvent_t ev[kSlots] = {};
@@ -1456,20 +1457,14 @@ bool capturing(const Engine& E) {
   return c != hipStreamCaptureStatusNone;
 }
 
-// a stream under capture refuses what reads or writes host memory: it takes
-// the general copies, which report that
-bool staged(const Engine& E, size_t row_bytes) {
-  return E.stage.n > 0 && row_bytes <= E.stage.slot && !capturing(E);
-}
-
 // bytes of a problem's fields
 size_t field_bytes(const bp_problem& p) { return (size_t)p.nx * p.ny * 6 * sizeof(double); }
 
-// staging for fields of up to `bytes`; without it (no memory) fields and loads
-// go through pageable copies
-void stage_init(Stage& S, size_t bytes) {
-  S.slot = std::min(Stage::kSlot, align_up(bytes));
-  const int n = (int)std::min<size_t>(Stage::kSlots, (bytes + S.slot - 1) / S.slot);
+// staging for fields of up to S.want bytes; without it (no memory) fields and
+// loads go through pageable copies
+void stage_init(Stage& S) {
+  S.slot = std::min(Stage::kSlot, align_up(S.want));
+  const int n = (int)std::min<size_t>(Stage::kSlots, (S.want + S.slot - 1) / S.slot);
   if (hipHostMalloc((void**)&S.mem, n * (S.slot + Stage::kHead), hipHostMallocDefault) != hipSuccess) {
     (void)hipGetLastError();
     S.mem = nullptr;
@@ -1485,6 +1480,24 @@ void stage_release(Stage& S) {
   for (int i = 0; i < S.n; ++i) (void)hipEventDestroy(S.ev[i]);
   if (S.mem) (void)hipHostFree(S.mem);
   S = Stage();
+}
+
+// What fits one slot is allocated with the engine (26 us, which the first fields
+// would pay alike); more than that when fields or loads first pass, since megabytes
+// of pinned memory cost a 512^2 solver 0.6 of the 3.0 ms of its creation and
+// one whose fields nobody reads needs none
+void stage_want(Stage& S, size_t bytes) {
+  S.want = bytes;
+  if (bytes <= Stage::kSlot) stage_init(S);
+}
+
+// do rows of this many bytes go through the staging slots?  A stream under
+// capture refuses what reads or writes host memory: it takes the general
+// copies, which report that
+bool staged(Engine& E, size_t row_bytes) {
+  if (capturing(E)) return false;
+  if (E.stage.want > 0 && !E.stage.mem) stage_init(E.stage);
+  return E.stage.n > 0 && row_bytes <= E.stage.slot;
 }
 
 void engine_release(Engine& E) {
@@ -2444,7 +2457,7 @@ bp_status create_solver(const bp_problem* p, const Layout& lo, char* w, void* hi
   s->ws = w;
   bp_status rc = engine_init(s->E, w + lo.total, need - lo.total, 1, te, st, lo.fdbl, lo.shift, p->K, p->ne_fixed,
                              p->cycle, no_alloc);
-  if (rc == BP_OK && !no_alloc) stage_init(s->E.stage, field_bytes(*p));
+  if (rc == BP_OK && !no_alloc) stage_want(s->E.stage, field_bytes(*p));
   s->E.csweeps = p->coarse_sweeps;
   s->E.lag = p->lag != 0;
   if (s->E.lag) s->E.fuse = false;  // the lag runs single applications
@@ -2936,7 +2949,7 @@ bp_status bp_batch_create(const bp_problem* probs, int32_t n, void* device_ws, s
                              probs[0].ne_fixed, probs[0].cycle);
   size_t most = 0;
   for (int i = 0; i < n; ++i) most = std::max(most, field_bytes(probs[i]));
-  if (rc == BP_OK) stage_init(b->E.stage, most);
+  if (rc == BP_OK) stage_want(b->E.stage, most);
   b->E.csweeps = probs[0].coarse_sweeps;
   off = 0;
   for (int i = 0; i < n && rc == BP_OK; ++i) {
@@ -3052,7 +3065,7 @@ bp_status bp_server_create(void* device_ws, size_t ws_bytes, void* hip_stream, i
     delete s;
     return rc;
   }
-  stage_init(s->E.stage, Stage::kSlots * Stage::kSlot);  // requests of any size
+  stage_want(s->E.stage, Stage::kSlots * Stage::kSlot);  // requests of any size
   s->pool.init(area, ws_bytes - area);
   *out = s;
   return BP_OK;
