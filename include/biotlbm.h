@@ -310,10 +310,10 @@ bp_status bp_destroy(bp_solver *s);
 
 /* For callers that cannot allocate (code under HIP graph capture, tight
  * serving loops, harnesses that forbid hipMalloc): bp_create on a workspace
- * the library owns, a file-scope static device array of 64 MiB and the coarse
- * levels' matrix (128 KiB) per device
- * (held from the library's first use on that device until the process ends;
- * a problem whose bp_workspace_bytes exceed it is refused with
+ * the library owns, a file-scope static device array of 64 MiB and 256 KiB (half
+ * of these for the coarse levels' matrix, half for work lists of small tiles) per
+ * device (held from the library's first use on that device until the process
+ * ends; a problem whose bp_workspace_bytes exceed it is refused with
  * BP_ERR_WORKSPACE).  The solver then allocates nothing: no device or pinned
  * host memory, and no captured graphs (its time steps launch their kernels
  * directly, with the same kernels and results as bp_create's solver).  The
@@ -333,9 +333,9 @@ bp_status bp_create_static(const bp_problem *p, void *hip_stream, bp_solver **ou
  * parameters and boundary data may differ.  Each problem's arithmetic is that
  * of solving it alone; results are bitwise identical when the batch leaves the
  * launch variants unchanged (a depth takes four-application launches, fuses
- * the restriction and picks the region width of four applications with the
- * restriction according to the cells it covers in all), and otherwise
- * agree to rounding (operations are fused differently in the variants). */
+ * the restriction and picks its regions according to the cells and blocks of
+ * its launches in all), and otherwise agree to rounding (operations are fused
+ * differently in the variants). */
 /* A problem whose state diverges (BP_ERR_DIVERGED above) leaves the batch at
  * the next check (every 8 steps of bp_batch_step, and at its end): its later
  * steps are not run, its fields stay those of the check, bp_batch_get_fields

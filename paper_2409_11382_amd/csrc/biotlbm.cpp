@@ -713,8 +713,8 @@ struct DepthLists {
 // pinned host memory in slots, through which fields leave and loads enter the
 // device: the fields kernel writes a slot directly and threads copy the slots
 // to the caller's arrays, whose page faults bound a large readout.  Fields by
-// pageable copies of whole planes -> by slots: 64^2 0.16 -> 0.03 ms, 512^2
-// 1.25 -> 0.50, 2048^2 (201 MB) 31 -> 9.5, the 48 of a batch 50 -> 16.
+// slots (by pageable copies of whole planes) in ms: 64^2 0.03 (0.16), 512^2 0.50
+// (1.25), 2048^2 (201 MB) 9.5 (31), the 48 of a batch 16 (50).
 // Slots of 512 KiB: writing one takes longer than launching its kernel.
 struct Stage {
   static constexpr size_t kSlot = 512 << 10;
@@ -834,14 +834,14 @@ int64_t depth_blocks(const Engine& E, int d, int A, bool alt) {
 // the chip's 256 CUs, so where a bound was not given the region with the
 // cheaper rounds is taken.  Measured times in us of one launch at n^2 cells:
 // - four applications on 32 x 32 regions: two blocks' rounds (at most 512
-//   blocks, and 256 with the restriction) against two pairs.  320^2: 17.1 for
-//   four, 23.2 for two pairs, with the restriction 17.6 against 27.6; 368^2,
-//   in a third and second round: 21.6 and 23.2, 27.9 and 27.8.
+//   blocks, and 256 with the restriction) against two pairs.  320^2: 18.6 for
+//   four, 25.4 for two pairs, with the restriction 18.4 against 28.3; 368^2,
+//   in a third and second round: 23.7 and 25.7, 27.9 and 28.7.
 // - four applications on regions of 24 rows while one round holds them (a 160^2
 //   step 228.4 us, on 32 rows 236.6; 128^2 in FP64 246.5 and 258).
-// - four with the restriction: narrow regions in one round (184 x 120 cells
-//   in 160 blocks: a 736 x 480 step 555, on wide ones 566), wide beyond (224^2
-//   in 361 narrow blocks: an 896^2 step 786, wide 778).
+// - four with the restriction: narrow regions in one round (184 x 120 cells in
+//   160 blocks 13.0, on wide ones 17.4), wide beyond (224^2 in 361 narrow blocks
+//   21.3, wide 18.1).
 // - pairs in FP32 shifted storage: tall regions (one block per CU) in one
 //   round, or in two where the default (two blocks per CU) takes two as well.
 //   Default and tall: 512^2 16.4 and 14.0 (one round each), 736^2 23.3 and
@@ -851,14 +851,17 @@ int64_t depth_blocks(const Engine& E, int d, int A, bool alt) {
 //   39.8, 1216^2 40.3 and 47.1, 1280^2 43.0 and 49.5, 1408^2 49.8 and 57.8,
 //   1536^2 59.1 and 69.8, 1824^2 85.2 and 106.6, 1920^2 96.0 and 118.2, 2048^2
 //   104.7 and 134.5.
-// - pairs in FP32: both regions have the same outputs; one per CU while one
-//   round suffices (512^2 12.8, two per CU 14.4), else two (1024^2 37.4, 32.0).
+// - pairs in FP32: both regions have the same outputs; one block per CU while
+//   one round suffices (512^2 13.1, two per CU 14.7), else two (736^2 20.8 and
+//   19.9, 1024^2 33.9 and 30.7).
 // - pairs in FP64: tall where that is one round and the default more than one
-//   (512^2 17.5 against 21.6; 320^2 16.2, 12.2; 1024^2 52.8, 44.1).
-// - pairs with the restriction: in FP32 likewise (shifted 512^2 19.2 against
-//   21.2, 384^2 18.3, 16.5, 1024^2 53.6, 48.5); in FP64 rounds of 16 waves x 2
-//   rows cost 8/9 of those of 12 x 3 (384^2 20.3 and 23.2; 512^2 31.3, 23.6;
-//   640^2 35.8, 39.1; 736^2 48.1, 43.0).
+//   (512^2 17.3 against 19.9; 384^2 16.4, 14.3; 736^2 29.9, 29.5; 1024^2 52.9,
+//   43.7).
+// - pairs with the restriction: in FP32 likewise (shifted 512^2 18.4 against
+//   19.7, 384^2 18.0, 16.3, 1024^2 54.8, 48.3); in FP64 rounds of 16 waves x 2
+//   rows cost 8/9 of those of 12 x 3 (384^2 20.2 and 23.2; 512^2 31.0, 23.2;
+//   640^2 35.6, 38.6; 736^2 49.0, 41.7; 1024^2 79.7, 74.4; 1280^2 115.1, 115.7;
+//   1824^2 225.9, 227.5; 2048^2 288.6, 278.7).
 void region_rules(const Engine& E, int d, int64_t cells, DepthLists& r) {
   const bool shift = E.shift && d == 0;
   if (E.wide && d == 0) return;  // pairs in the default region
@@ -2174,7 +2177,7 @@ std::string op_name(const Op& o) {
 // by the process until it ends.  In host code `scratch` names a host-side
 // stand-in, never a device address: the device address comes from
 // hipGetSymbolAddress, once per device with that device current.
-// 64 MiB, a coarse matrix and the tile lists of low regions
+// 64 MiB, the coarse levels' matrix and 128 KiB for tile lists of low regions
 constexpr size_t kScratchBytes = (size_t(64) << 20) + tail_matrix_bytes(kTailDenseCells) + (128 << 10);
 static __device__ __align__(256) char scratch[kScratchBytes];
 constexpr int kMaxDevices = 64;

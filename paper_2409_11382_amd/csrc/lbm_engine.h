@@ -205,8 +205,8 @@ hipError_t launch_tsweep(const SweepL& a, int ntiles, hipStream_t s);
 //   rows (12 waves x 3), 24 output rows, one block per CU on a 512^2 level and
 //   less halo work; FP64 shifted storage lacks the LDS and keeps 8 waves.
 //   FP64 with the restriction has LDS for one block per CU in either form: 16
-//   waves x 2 rows, 20 output rows (1024^2: 77 us, ALT 76; 8 waves x 3 rows,
-//   which left the SIMDs two waves each, took 89).
+//   waves x 2 rows, 20 output rows (1024^2: 80 us, ALT 74; 8 waves x 3 rows,
+//   which leave the SIMDs two waves each, 89).
 // - four applications are used only on depths of few cells, where the launch
 //   is bound by the dependent work of one block: a 32 x 32 region (16 x 16
 //   outputs) spreads such a depth over about four times as many compute units
@@ -261,8 +261,8 @@ inline hipError_t launch_tsweep2(const SweepL& a, int ntiles, hipStream_t s) {
   return launch_tsweep2<T, Tc, FINE, SHIFT, APPS, RES, ALT>(a, ntiles, false, s);
 }
 // pairs on the finest level in the default region for planes of 4 GiB and more;
-// references in either precision, per problem.  Single applications took 382 ms
-// for a step of two cycles on 32768 x 16384 cells in FP32 shifted, pairs 204
+// references in either precision, per problem.  A step of two cycles on 32768 x
+// 16384 cells in FP32 shifted takes 204 ms, by single applications 382
 template <typename T, typename Tc, bool SHIFT, bool RES>
 hipError_t launch_tsweep2_wide(const SweepL& a, int ntiles, hipStream_t s);
 template <typename T, bool SHIFT>

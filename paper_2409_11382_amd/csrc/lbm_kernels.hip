@@ -351,12 +351,14 @@ hipError_t launch_tsweep(const SweepL& a, int ntiles, hipStream_t s) {
 // divergence's ghost is the wall cell itself (an index), a wall population is
 // read from its mirror image or its opposite by a selected LDS offset, the
 // reference's share joins the correction that every pull adds anyway, and the
-// halfway rules' data wait in LDS.  Against per-lane branches over wall types,
-// a ghost-row pass behind its own barrier and loads of the data in every
-// application, a 64^2 level's launch of four applications drops from 14.9 to
-// 12.3 us (with the restriction from 15.4 to 13.1), the 512^2 pair from 16.2
-// to 15.0 us and the 512^2 FP32-shifted step from 580 to 515 us; periodic
-// levels, which have no walls, take 11.0 and 13.3 us.
+// halfway rules' data wait in LDS.  Branches per lane over the wall types, a
+// ghost-row pass behind its own barrier and loads of the data in every
+// application cost 12 to 20% of a launch on depths of few cells.
+// Launches in FP32 shifted (FP64), us: four applications at 64^2 11.2 (12.3),
+// with the restriction 12.8 (14.9); pairs at 512^2 13.9 (17.5), with the
+// restriction 18.5 (22.9); at 1024^2 33.8 (43.6) and 48.0 (74.0); at 2048^2 105
+// and 164, the pair at 3.4 TB/s of HBM and 60% of the vector issue: two blocks
+// a CU do not cover each other's loads and barriers fully.
 // R64: shifted storage whose references may be FP64 (FP64 populations, or a
 // problem above the size where FP32 references lose accuracy); without it the
 // reference arithmetic is FP32 only.
@@ -394,8 +396,8 @@ __global__ __launch_bounds__((kWave * sweepn_waves<T, SHIFT, APPS + RES, ALT>())
   static_assert(!WIDE || (FINE && S == 1), "a wave holds one row of the finest level");
 
   const int2 te = a.tiles[blockIdx.x];
-  // the entry names the level too: one dependent descriptor load less (steps of
-  // 512^2 424 -> 422.5 us, in FP64 555.5 -> 553)
+  // the entry names the level too: one dependent descriptor load less (1.5 us of
+  // a 512^2 step)
   const ProbD& P = a.probs[te.x & ((1 << kTileLevelShift) - 1)];
   const int l = te.x >> kTileLevelShift;
   const LevelD& V = P.lv[l];
@@ -433,15 +435,13 @@ __global__ __launch_bounds__((kWave * sweepn_waves<T, SHIFT, APPS + RES, ALT>())
   T Rv[FINE ? 1 : NK][8];
   T Fx[FINE ? NK : 1], Fy[FINE ? NK : 1];
 
-  // ---- load the region: every lane loads, from 32-bit byte offsets.  A launch
-  // is a chain of about 650 instructions before its first application if each
-  // load sits in a branch of its own with a 64-bit address and ghosts and tiles
-  // are found by integer division; in this form it is about 400, and the 64^2
-  // launch of four applications takes 7.8 instead of 8.7 us, the 512^2 pair
-  // 11.3 instead of 12.0 and the 2048^2 pair 108 instead of 118.  The loads of
-  // every row are issued before the first value is used (the reference's way
-  // to LDS and the coarse correction would make each row wait for its own):
-  // 1024^2 pairs 35.7 -> 33.4 us, 2048^2 108.7 -> 104.8
+  // ---- load the region: every lane loads, from 32-bit byte offsets.  With each
+  // load in a branch of its own, a 64-bit address per lane and ghosts and tiles
+  // found by integer division, the chain before the first application is 650
+  // instructions, in this form 400, and a launch about 8% shorter at every size.
+  // The loads of every row are issued before the first value is used: the
+  // reference's way to LDS and the coarse correction would make each row wait
+  // for its own (5% of a pair)
   uint32_t off[NK], coff[NK];  // byte offset of the row's cell in a plane, of its coarse cell in a coarse plane
   int64_t row[WIDE ? NK : 1];  // WIDE: the row's first cell, and off counts from there
   auto at = [&](auto base, int kk) {
@@ -979,9 +979,9 @@ __device__ __forceinline__ void finalize_norms(const ProbL& a, int pid, double* 
 // ones: every load of both rows of a lane is issued before the first use, from
 // offsets without branches (ghost cells are copies: an index), and 8 waves of
 // 2 rows keep more loads in flight than 4 of 4.  Types of wall cells are read in
-// tiles that hold a wall.  With the norms' launch of its own, before -> now:
-// 64^2 20 -> 12 us, 512^2 23.6 -> 17.4, 2048^2 149 -> 132 (144 bytes per cell,
-// 4.6 TB/s), 1024^2 in FP64 66 -> 55.
+// tiles that hold a wall.  64^2 11.7 us, 512^2 16.7, 2048^2 132 (144 bytes per
+// cell, 4.6 TB/s), 1024^2 in FP64 55; with 4 waves of 4 rows and a launch of its
+// own for the norms 20, 23.6, 149 and 66.
 template <typename T, bool SHIFT>
 __global__ __launch_bounds__((kWave * kFlowWaves)) void k_tflow(CellL a) {
   if (gated_off(a.skip, a.need)) return;  // uniform over the grid
@@ -1661,7 +1661,7 @@ __device__ __forceinline__ ElConst<T> tail_consts(const ProbD& P) {
 }
 
 // a level of one wave needs no barrier between its own LDS writes and reads
-// (in FP32: 64^2 tail 30.3 -> 29.1 us; in FP64 it gained nothing)
+// (in FP32 1.2 us of a tail; in FP64 it gained nothing)
 template <typename T> __device__ __forceinline__ void tail_sync(int n) {
   if (sizeof(T) == 8 || __builtin_expect(n > kWave, 1)) {  // uniform
     __syncthreads();
@@ -1677,7 +1677,7 @@ template <typename T> __device__ __forceinline__ void tail_sync(int n) {
 // G <- G - S(G) (residual).  Two barriers; sD and sG may be reused right after
 // the return.  sG's planes have PS cells whatever the level, so that planes and
 // tables are LDS addresses as they stand (50 of a sweep's 170 vector
-// instructions were address arithmetic and unpacking; FP64 tail 42.0 -> 40.5 us).
+// instructions were address arithmetic and unpacking, 1.5 us of an FP64 tail).
 template <typename T, int PS = kTailThreads>
 __device__ __forceinline__ void tail_relax(const ElConst<T>& k, int n, const TailTab& tb, T (&G)[1][8],
                                            const T (&R)[1][8], T* sD, T* sG, bool blend) {
@@ -1803,9 +1803,7 @@ __device__ __forceinline__ void tail_zero(T (&A)[1][8]) {
 // right-hand side, and its 17 sweeps of one wave each (two levels, K = 4) are
 // a chain of about 12 us, while the map's 128 x 128 matrix is read in under
 // one.  It is formed once per problem in FP64 (k_tail_matrix) and applied in
-// FP64 to the right-hand side as the sweeps would receive it.  Measured, tail
-// of a 512^2 problem: 46.1 -> 33.3 us in FP32, 61 -> 45 in FP64 (with row
-// numbers by multiplication and first sweeps without a D exchange).
+// FP64 to the right-hand side as the sweeps would receive it.
 constexpr int kTailPart = 8;  // threads per row of the matrix
 
 // G = V-cycle on levels l..1 (at most kTailDenseCells cells each) from zero
@@ -1932,11 +1930,11 @@ __device__ __forceinline__ void tail_dense(const ProbD& P, const TR (&R)[1][8], 
   __syncthreads();
 }
 
-// The tail is one workgroup's chain: of 34 us (32^2 on top, FP32) 16 were its
-// sweeps, the rest the way between levels.  Level descriptors are read as
-// constant memory, whose loads need not follow every store and barrier anew:
-// with the matrix warmed 34.3 -> 31.0 us, and 50 cycles of an 8 x 128 column
-// (k_tail_full) 2.07 -> 1.69 ms in FP64, 1.81 -> 1.42 in FP32.
+// The tail is one workgroup's chain.  From 32^2 on it takes 29 us in FP32 and 38
+// to 41 in FP64, about half of them its sweeps, the rest the way between levels.
+// Level descriptors are read as constant memory, whose loads need not follow
+// every store and barrier anew: in k_tail_full, 50 cycles of an 8 x 128 column,
+// 1.69 ms in FP64 (2.07 without) and 1.42 in FP32 (1.81).
 // Algorithm 4 on levels lt..1 of one problem; levels >= 2 are stored as T,
 // level 1 as T1.  Thread c owns cell c of every level.  Going down, the
 // restricted residual of a level stays in the registers of the thread that
@@ -1961,7 +1959,7 @@ __device__ __forceinline__ void tail_run(const ProbD& P, int lt, int K, char* ld
     tail_load1<T>(P.lv[lt], P.lv[lt].r, c, R);
   else
     tail_load1<T1>(P.lv[1], P.lv[1].r, c, R1);
-  // the matrix (read cold at the turn, it took 4.4 of the tail's 34 us): in FP32
+  // the matrix (read cold at the turn it takes 4.4 us): in FP32
   // fetched before the sweeps of the level above, in FP64, which lacks the
   // registers, brought into this XCD's L2 behind the first sweeps, a word of
   // each 128-byte line
@@ -2374,9 +2372,7 @@ __device__ __forceinline__ void tail_relax_fine(const ElConst<T>& k, int n, cons
 // the finest level's force and wall terms, loaded into LDS once per launch
 // (every phase of every cycle uses them; registers held across the phases
 // would spill): 8 planes of wall terms, then the force's two.  A serial chain
-// of sweeps bounds the launch; the Terzaghi column 8 x 128 in FP64, 50 cycles:
-// 2.22 ms per step with global loads in each phase, 2.07 so (1.69 with
-// constant descriptors)
+// of sweeps bounds the launch (loads in each phase cost 7% of it)
 template <typename T>
 __device__ __forceinline__ bool tail_fine_load(const ProbD& P, const LevelD& V, T* sF) {
   const int c = threadIdx.x;
