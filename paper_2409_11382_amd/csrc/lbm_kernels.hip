@@ -357,7 +357,7 @@ hipError_t launch_tsweep(const SweepL& a, int ntiles, hipStream_t s) {
 // Launches in FP32 shifted (FP64), us: four applications at 64^2 11.2 (12.3),
 // with the restriction 12.8 (14.9); pairs at 512^2 13.9 (17.5), with the
 // restriction 18.5 (22.9); at 1024^2 33.8 (43.6) and 48.0 (74.0); at 2048^2 105
-// and 164, the pair at 3.4 TB/s of HBM and 60% of the vector issue: two blocks
+// and 164, the pair at 3.4 TB/s of HBM and half of the vector issue: two blocks
 // a CU do not cover each other's loads and barriers fully.
 // R64: shifted storage whose references may be FP64 (FP64 populations, or a
 // problem above the size where FP32 references lose accuracy); without it the
